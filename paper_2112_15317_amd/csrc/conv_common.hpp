@@ -4,6 +4,7 @@
 #pragma once
 
 #include "sb_internal.hpp"
+#include "split_bf16.hpp"
 
 #include <type_traits>
 
@@ -199,6 +200,58 @@ __global__ __launch_bounds__(256) void filter_pack(const E* __restrict__ w, E* _
   pack_slice<DGRAD, CK, BN, E, LAYOUT>(w, out, Cin, Cout, blockIdx.x, slice_lds);
 }
 
+// Packed filters of the split fp32 kernels (conv_split.hip): slice (16 output
+// channels, 32 input channels) = 9 taps x 3 parts (high, mid, low) x the 512
+// bf16 of one MFMA operand in lane order, [ci / 8][co][ci % 8].  The slice is
+// read in the filters' own order (runs of 288 elements per output channel, or
+// 144 per input channel for the data gradient), permuted in LDS as
+// [tap * 32 + ci][co] and split as it leaves.
+constexpr int kSplitSlice = 9 * 3 * 512, kSplitRow = 17, kSplitSliceLds = 9 * 32 * kSplitRow;
+template <bool DGRAD>
+__device__ __forceinline__ void pack_split_slice(const float* __restrict__ w,
+                                                 u16* __restrict__ out, int Cin, int Cout,
+                                                 int slice, float* slice_lds) {
+  constexpr int SL = 9 * 32 * 16;
+  static_assert(SL % 256 == 0, "whole rounds");
+  const int nchunks = cdiv(Cin, 32);
+  const int co0 = slice / nchunks * 16, c0 = slice % nchunks * 32;
+  float v[SL / 256];
+#pragma unroll
+  for (int i = 0; i < SL / 256; ++i) {
+    const int g = threadIdx.x + i * 256;
+    int cc, nn, t;
+    if (!DGRAD) { nn = g / 288; cc = g % 288 / 9; t = g % 9; }
+    else { cc = g / 144; nn = g % 144 / 9; t = g % 9; }
+    const bool ok = co0 + nn < Cout && c0 + cc < Cin;
+    v[i] = ok ? w[DGRAD ? ((size_t)(c0 + cc) * Cout + co0 + nn) * 9 + t
+                        : ((size_t)(co0 + nn) * Cin + c0 + cc) * 9 + t] : 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < SL / 256; ++i) {
+    const int g = threadIdx.x + i * 256;
+    int cc, nn, t;
+    if (!DGRAD) { nn = g / 288; cc = g % 288 / 9; t = g % 9; }
+    else { cc = g / 144; nn = g % 144 / 9; t = 8 - g % 9; }
+    slice_lds[(t * 32 + cc) * kSplitRow + nn] = v[i];
+  }
+  __syncthreads();
+  u16* dst = out + (size_t)slice * kSplitSlice;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {                      // 9 taps x 64 lanes of 8 channels
+    const int q = threadIdx.x + i * 256, lane = q & 63, t = q >> 6;
+    if (t >= 9) break;
+    s8 p[3];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      u16 h, m, l;
+      split_stored(slice_lds[(t * 32 + (lane >> 4) * 8 + j) * kSplitRow + (lane & 15)], h, m, l);
+      p[0][j] = (short)h; p[1][j] = (short)m; p[2][j] = (short)l;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) *reinterpret_cast<s8*>(dst + (t * 3 + k) * 512 + lane * 8) = p[k];
+  }
+}
+
 // Several layers' (and passes') filters in one launch: a pack task per
 // (filters, pass); the blocks of task t are block0[t] .. block0[t+1]-1, one
 // per slice.  `kind` names the slice geometry (pack_kind()).  One launch
@@ -223,9 +276,11 @@ __host__ __device__ constexpr int pack_kind(bool dgrad, int layout, int ck, int 
          ((bn == 16 ? 0 : bn == 32 ? 1 : 2) << 4);
 }
 
-// fp32 filters only take the PackCO kinds (the bf16 kernels' PackCI8 slices
-// are bf16), so the fp32 kernel sizes its LDS for those alone: the larger
-// PackCI8 buffer would cut the resident blocks per CU by more than half.
+// fp32 filters take the PackCO kinds or the split kernels' slices (the bf16
+// kernels' PackCI8 slices are bf16), so the fp32 kernel sizes its LDS for
+// those alone: the larger PackCI8 buffer would cut the resident blocks per CU
+// by more than half.
+constexpr int kPackSplitFwd = 128, kPackSplitBwd = 129;
 template <class E>
 __global__ __launch_bounds__(256) void filter_pack_many(PackBatch b) {
   constexpr bool F32 = std::is_same<E, float>::value;
@@ -233,7 +288,8 @@ __global__ __launch_bounds__(256) void filter_pack_many(PackBatch b) {
                                   slice_lds_elems<8, 64, E, PackCO>()
                           ? slice_lds_elems<16, 64, E, PackCI8>()
                           : slice_lds_elems<8, 64, E, PackCO>();
-  __shared__ E slice_lds[LDS];
+  static_assert(!F32 || kSplitSliceLds <= LDS + 256, "about the same LDS");
+  __shared__ E slice_lds[F32 && kSplitSliceLds > LDS ? kSplitSliceLds : LDS];
   const int blk = blockIdx.x;
   int t = 0;
   while (t + 1 < b.ntasks && b.block0[t + 1] <= blk) ++t;
@@ -253,7 +309,12 @@ __global__ __launch_bounds__(256) void filter_pack_many(PackBatch b) {
     SB_PACK_CASE(false, PackCO, 8, 16)
     SB_PACK_CASE(true, PackCO, 8, 16)
     default:
-      if constexpr (!F32) {
+      if constexpr (F32) {
+        if (k.kind == kPackSplitFwd)
+          pack_split_slice<false>(w, (u16*)k.out, k.Cin, k.Cout, slice, slice_lds);
+        else if (k.kind == kPackSplitBwd)
+          pack_split_slice<true>(w, (u16*)k.out, k.Cin, k.Cout, slice, slice_lds);
+      } else {
         switch (k.kind) {
           SB_PACK_CASE(false, PackCI8, 16, 64)
           SB_PACK_CASE(true, PackCI8, 16, 64)
@@ -371,6 +432,18 @@ __global__ __launch_bounds__(256) void conv_splitk_reduce_pool(
   const bool pos = m > 0.f;
   Elem<E>::store(out, q, pos ? m : 0.f);
   idx[q] = (uint8_t)(c | (pos ? 0u : 0x80u));
+}
+
+template <class E>
+inline void launch_splitk_reduce_pool(const ConvArgs& a, int splits, size_t total,
+                                      hipStream_t st) {
+  const unsigned pg = (unsigned)((total / 4 + 255) / 256);
+  if (((uintptr_t)a.part & 7) == 0)
+    conv_splitk_reduce_pool<E, true><<<pg, 256, 0, st>>>(a.part, splits, total, a.Cout, a.H, a.W,
+                                                         a.bias, (E*)a.out, a.pool_idx);
+  else
+    conv_splitk_reduce_pool<E, false><<<pg, 256, 0, st>>>(a.part, splits, total, a.Cout, a.H, a.W,
+                                                          a.bias, (E*)a.out, a.pool_idx);
 }
 
 // Launches the split reduction of a convolution pass: the 4-wide form when

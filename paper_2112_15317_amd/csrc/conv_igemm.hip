@@ -1023,13 +1023,8 @@ static void igemm_launch(const IgemmPlan& p, const ConvArgs& a, bool pack, hipSt
   }
   if (p.splits > 1) {
     size_t total = (size_t)a.N * a.Cout * a.H * a.W;
-    const unsigned pg = (unsigned)((total / 4 + 255) / 256);
-    if (a.pool_idx && ((uintptr_t)a.part & 7) == 0)   // pooled forward: the reduction pools
-      conv_splitk_reduce_pool<E, true><<<pg, 256, 0, st>>>(
-          a.part, p.splits, total, a.Cout, a.H, a.W, a.bias, (E*)a.out, a.pool_idx);
-    else if (a.pool_idx)
-      conv_splitk_reduce_pool<E, false><<<pg, 256, 0, st>>>(
-          a.part, p.splits, total, a.Cout, a.H, a.W, a.bias, (E*)a.out, a.pool_idx);
+    if (a.pool_idx)                                   // pooled forward: the reduction pools
+      launch_splitk_reduce_pool<E>(a, p.splits, total, st);
     else
       launch_splitk_reduce<E>(a.part, p.splits, total, a.Cout, a.H * a.W, a.bias, a.relu,
                               (const E*)a.mask, (E*)a.out, st);
@@ -1133,11 +1128,27 @@ sb_status conv_bf16(bool dgrad, int N, int Cin, int H, int W, int Cout, const vo
                     const void* wt, const float* bias, const void* mask, void* out, void* ws,
                     size_t ws_bytes, int relu, bool prepacked, hipStream_t st);
 
+// The split fp32 path (conv_split.hip) for the fp32 shapes it takes.
+bool conv_split_takes(int Cin, int W, int Cout);
+size_t conv_split_ws(int N, int Cin, int H, int W, int Cout, bool prepacked);
+size_t conv_split_pack_bytes(int N, int Cin, int H, int W, int Cout);
+void conv_split_pack(bool dgrad, int Cin, int Cout, const void* wt, void* packed, hipStream_t st);
+int conv_split_describe(bool dgrad, int N, int Cin, int H, int W, int Cout, char* buf, size_t len,
+                        bool pool);
+sb_status conv_split(bool dgrad, int N, int Cin, int H, int W, int Cout, const void* in,
+                     const void* wt, const float* bias, const void* mask, void* out, void* ws,
+                     size_t ws_bytes, int relu, bool prepacked, hipStream_t st,
+                     uint8_t* pool_idx);
+static bool split_takes(int dtype, int Cin, int W, int Cout) {
+  return dtype == SB_F32 && conv_split_takes(Cin, W, Cout);
+}
+
 // Workspace of a forward / data-gradient call; prepacked: the filters come
 // packed, the workspace holds only the split partials.
 size_t conv_igemm_ws(int dtype, int N, int Cin, int H, int W, int Cout, bool prepacked) {
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16_ws(N, Cin, H, W, Cout, prepacked);
+  if (split_takes(dtype, Cin, W, Cout)) return conv_split_ws(N, Cin, H, W, Cout, prepacked);
   const int es = (int)dsize(dtype);
   const sb::IgemmPlan p = sb::igemm_plan(N, Cin, H, W, Cout, es, true);
   const sb::IgemmPlan q = sb::igemm_plan(N, Cin, H, W, Cout, es, false);
@@ -1151,6 +1162,7 @@ size_t conv_igemm_ws(int dtype, int N, int Cin, int H, int W, int Cout, bool pre
 size_t conv_igemm_pack_bytes(int dtype, int N, int Cin, int H, int W, int Cout) {
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16_pack_bytes(N, Cin, H, W, Cout);
+  if (split_takes(dtype, Cin, W, Cout)) return conv_split_pack_bytes(N, Cin, H, W, Cout);
   return sb::igemm_plan(N, Cin, H, W, Cout, (int)dsize(dtype), false).pack_bytes;
 }
 
@@ -1160,6 +1172,14 @@ void conv_bf16_pack_geom(int N, int Cin, int H, int W, int Cout, int* ck, int* b
 // number of slices of a forward or data-gradient packing.
 int conv_igemm_pack_task(bool dgrad, int dtype, int N, int Cin, int H, int W, int Cout,
                          const void* wt, void* packed, sb::PackTask* t) {
+  t->w = wt;
+  t->out = packed;
+  t->Cin = Cin;
+  t->Cout = Cout;
+  if (split_takes(dtype, Cin, W, Cout)) {
+    t->kind = dgrad ? sb::kPackSplitBwd : sb::kPackSplitFwd;
+    return sb::cdiv(Cout, 16) * sb::cdiv(Cin, 32);
+  }
   int ck, bn, slices, layout;
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout)) {
     conv_bf16_pack_geom(N, Cin, H, W, Cout, &ck, &bn, &slices);
@@ -1171,10 +1191,6 @@ int conv_igemm_pack_task(bool dgrad, int dtype, int N, int Cin, int H, int W, in
     slices = p.co_tiles * p.nchunks;
     layout = sb::PackCO;
   }
-  t->w = wt;
-  t->out = packed;
-  t->Cin = Cin;
-  t->Cout = Cout;
   t->kind = sb::pack_kind(dgrad, layout, ck, bn);
   return slices;
 }
@@ -1191,6 +1207,10 @@ void conv_igemm_pack(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
     conv_bf16_pack(dgrad, N, Cin, H, W, Cout, wt, packed, st);
     return;
   }
+  if (split_takes(dtype, Cin, W, Cout)) {
+    conv_split_pack(dgrad, Cin, Cout, wt, packed, st);
+    return;
+  }
   const sb::IgemmPlan p = sb::igemm_plan(N, Cin, H, W, Cout, (int)dsize(dtype), false);
   if (dtype == SB_BF16) {
     if (dgrad) sb::igemm_pack<true, sb::u16>(p, wt, packed, Cin, Cout, st);
@@ -1205,6 +1225,7 @@ void conv_igemm_pack(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
 // even image sizes, and a plan that pools for aligned and unaligned tensors.
 bool conv_igemm_pools(int dtype, int N, int Cin, int H, int W, int Cout) {
   if (dtype != SB_F32 || H % 2 || W % 2) return false;
+  if (split_takes(dtype, Cin, W, Cout)) return true;
   for (bool aligned : {true, false})
     if (!sb::igemm_pools(sb::igemm_plan(N, Cin, H, W, Cout, 4, aligned), Cout)) return false;
   return true;
@@ -1214,6 +1235,8 @@ int conv_igemm_describe(bool dgrad, int dtype, int N, int Cin, int H, int W, int
                         char* buf, size_t len, bool pool) {
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16_describe(dgrad, N, Cin, H, W, Cout, buf, len);
+  if (split_takes(dtype, Cin, W, Cout))
+    return conv_split_describe(dgrad, N, Cin, H, W, Cout, buf, len, pool);
   sb::IgemmPlan p = sb::igemm_plan(N, Cin, H, W, Cout, (int)dsize(dtype));
   const char* et = dtype == SB_BF16 ? "unsigned short" : "float";
   if (sb::few_takes(p, Cout))
@@ -1238,6 +1261,9 @@ sb_status conv_igemm(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16(dgrad, N, Cin, H, W, Cout, in, wt, bias, mask, out, ws, ws_bytes, relu,
                      prepacked, st);
+  if (split_takes(dtype, Cin, W, Cout))
+    return conv_split(dgrad, N, Cin, H, W, Cout, in, wt, bias, mask, out, ws, ws_bytes, relu,
+                      prepacked, st, pool_idx);
   // The whole-image kernels move 4 elements at a time (16 bytes in fp32, 8 in
   // bf16); the plan only picks them for tensors aligned that far.
   const uintptr_t amask = dtype == SB_BF16 ? 7 : 15;
