@@ -1617,13 +1617,30 @@ static int wg_bf16_vec(int W, const void* x, const void* dy) {
   return 1;
 }
 
+// The split fp32 path (conv_wgrad_split.hip) for the fp32 shapes it takes.
+bool conv_wgrad_split_takes(int C, int H, int W);
+size_t conv_wgrad_split_ws(int N, int C, int H, int W, int K);
+int conv_wgrad_split_describe(int N, int C, int H, int W, int K, char* buf, size_t len);
+sb_status conv_wgrad_split(int N, int C, int H, int W, int K, const void* x, const void* dy,
+                           float* dw, float* db, void* ws, size_t ws_bytes, hipStream_t st);
+void conv_wgrad_reduce(const float* part, int splits, int K, int C, float* dw, float* db,
+                       hipStream_t st) {
+  sb::launch_splits_reduce(part, splits, K, C, dw, db, st);
+}
+static bool wgrad_split_takes(int dtype, int C, int H, int W) {
+  return dtype == SB_F32 && conv_wgrad_split_takes(C, H, W);
+}
+
 size_t conv_wgrad_ws(int dtype, int N, int C, int H, int W, int K) {
+  if (wgrad_split_takes(dtype, C, H, W)) return conv_wgrad_split_ws(N, C, H, W, K);
   const bool bf16 = dtype == SB_BF16;
   return std::max(sb::wg_plan(N, C, H, W, K, true, bf16).ws_bytes,
                   sb::wg_plan(N, C, H, W, K, false, bf16).ws_bytes);
 }
 
 int conv_wgrad_describe(int dtype, int N, int C, int H, int W, int K, char* buf, size_t len) {
+  if (wgrad_split_takes(dtype, C, H, W))
+    return conv_wgrad_split_describe(N, C, H, W, K, buf, len);
   sb::WgPlan p = sb::wg_plan(N, C, H, W, K, true, dtype == SB_BF16);
   char name[160];
   static const char* kBTiles[] = {"2, 32", "4, 16", "8, 8"};
@@ -1692,6 +1709,8 @@ static void wg_dispatch(const sb::WgPlan& p, const sb::WgArgs& a, hipStream_t st
 
 sb_status conv_wgrad(int dtype, int N, int C, int H, int W, int K, const void* x, const void* dy,
                      float* dw, float* db, void* ws, size_t ws_bytes, hipStream_t st) {
+  if (wgrad_split_takes(dtype, C, H, W))
+    return conv_wgrad_split(N, C, H, W, K, x, dy, dw, db, ws, ws_bytes, st);
   // The whole-image kernel moves 4 elements at a time (16 bytes in fp32, 8
   // in bf16).
   const uintptr_t amask = dtype == SB_BF16 ? 7 : 15;
@@ -1733,7 +1752,7 @@ sb_status conv_wgrad(int dtype, int N, int C, int H, int W, int K, const void* x
 // layer that takes another kernel (it runs on its own).
 int conv_wgrad_batch_key(int dtype, int N, int C, int H, int W, int K, const void* x,
                          const void* dy) {
-  if (dtype != SB_F32) return -1;
+  if (dtype != SB_F32 || conv_wgrad_split_takes(C, H, W)) return -1;
   const bool aligned = (((uintptr_t)x | (uintptr_t)dy) & 15) == 0;
   const sb::WgPlan p = sb::wg_plan(N, C, H, W, K, aligned, false);
   if (p.bc != 0 || p.tile > 2) return -1;

@@ -1,0 +1,464 @@
+// conv_wgrad_split.hip -- 3x3 / stride 1 / pad 1 convolution weight and bias
+// gradients of fp32 tensors on the bf16 MFMA, every fp32 operand split in
+// three bf16 parts (split_bf16.hpp):
+//   dw[k,c,r,s] = sum_{n,h,w} x[n,c,h+r-1,w+s-1] * dy[n,k,h,w]
+//   db[k]       = sum_{n,h,w} dy[n,k,h,w]
+//
+// GEMM view: rows = output channels k, columns = input channels c at each of
+// the 9 taps, reduction = pixels.  A block of 512 threads has a CU to itself
+// and owns 64 k x 16 c x 9 taps over a contiguous range of 128-pixel tiles:
+// four waves stage the next tile while four multiply, each the block's whole
+// output for 32 of the tile's pixels (one 16x16x32 MFMA step: 4 x 9 blocks of
+// 16 k x 16 c, 216 MFMAs).  The four waves' sums are added in wave order
+// through LDS at the end, so a block writes 37 KB of partials for its share of
+// the pixels, a fourth of what four waves with output blocks of their own
+// would (all accumulators of the chip are 38 MB).
+//
+//   * Staging: a lane loads 8 channels of 4 consecutive pixels as fp32 NCHW
+//     (16-byte loads where rows are whole aligned quads), splits them, and
+//     stores each pixel as three 16-byte pieces [part][channel / 8][pixel]
+//     [channel % 8]; the x tile is a halo, zero outside the image, so a tap is
+//     a constant offset.
+//   * An MFMA lane needs 8 consecutive pixels of one channel: two LDS
+//     transpose loads (ds_read_b64_tr_b16), each over 4 pixels x 16 channels,
+//     at any pixel offset, so no shifted copies.
+//   * The staging waves of the first column tile's blocks add up the dy values
+//     they load: the bias gradient.
+//
+// Measured (us, batch 128, the fp32-MFMA kernel before): 32x32 64 -> 64 channels
+// 97 -> 59, 16x16 128 channels 92 -> 54, 8x8 256 channels 87 -> 56, 4x4 512
+// channels 68 -> 53; 27x45, 75 -> 107 channels, batch 19: 79 -> 53.  With 4-byte
+// staging loads, 48 a lane and tile, the loads bound it (95 us at 16x16).
+//
+// The pixels are split over blocks when the output tiles do not fill the 256
+// CUs; each split writes its sums to the workspace and they are added in split
+// order.  No atomics: repeated calls give the same bits.
+#include "split_bf16.hpp"
+
+#include <algorithm>
+#include <cstdio>
+#include <mutex>
+#include <type_traits>
+
+namespace sb {
+
+struct WsArgs {
+  const float* x;        // [N][C][H][W]
+  const float* dy;       // [N][K][H][W]
+  float* dw;             // [K][C][3][3]
+  float* db;             // [K] or null
+  float* part;           // split partials: [splits][K*C*9 + K] (dw, then db)
+  int N, C, H, W, K;
+  int tiles_w, tiles_h, ptiles, tiles_per_split, c_tiles, splits;
+};
+
+template <int TH_, int TW_, int IMGS_>
+struct WsTile {
+  static constexpr int TH = TH_, TW = TW_, IMGS = IMGS_, BP = IMGS * TH * TW;
+  static_assert(BP == 128 && TW % 4 == 0, "128 pixels, groups of 4 within a row");
+  static constexpr int BK = 64, BC = 16;
+  static constexpr int HH = TH + 2, HW = TW + 2, PLANE = IMGS * HH * HW;
+  // Pixels per 8-channel plane in LDS: 4 modulo 16 (64 bytes), so the two
+  // planes of a transpose load lie in different banks.
+  static constexpr int DPL = BP + 4, XPL = (PLANE + 15) / 16 * 16 + 4;
+  static constexpr int DPART = 8 * DPL * 8, XPART = 2 * XPL * 8;     // bf16
+  static constexpr int LDS_DY = 3 * DPART, BUF = LDS_DY + 3 * XPART;
+  // Staging tasks of 8 channels: dy quads of 4 pixels (one per staging lane),
+  // x quads of 4 interior halo columns, single pixels of the two edge columns.
+  static_assert(BK / 8 * BP / 4 == 256, "a dy quad per lane");
+  static constexpr int XQ = 2 * IMGS * HH * (TW / 4), XE = 2 * IMGS * HH * 2;
+  static_assert(XQ <= 256 && XE <= 256, "at most one of each per lane");
+  // Block output in LDS: 4 copies of 64 rows of 16 c x 9 taps, then db.
+  static constexpr int RP = BC * 9 + 4, COPY = BK * RP;
+  static constexpr size_t LDS_STAGE = 2 * (size_t)BUF * sizeof(u16);
+  static constexpr size_t LDS_OUT = (4 * COPY + 64) * sizeof(float);
+  static constexpr size_t LDS_BYTES = LDS_STAGE > LDS_OUT ? LDS_STAGE : LDS_OUT;
+  static_assert(LDS_BYTES <= 160 * 1024, "one block per CU");
+  __host__ __device__ static constexpr int hp(int p) {   // halo pixel of tile pixel p at tap (0, 0)
+    return (p / (TH * TW) * HH + p / TW % TH) * HW + p % TW;
+  }
+};
+
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+
+__device__ __forceinline__ s8 tr8(const u16* lo, const u16* hi) {
+  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)lo);
+  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)hi);
+  return s8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+}
+
+// One element of dw in plain fp32 over the pixel tiles [pt0, pt1).
+template <class T>
+__device__ __forceinline__ float wgrad_one(const WsArgs& a, int k, int c, int tap, int pt0,
+                                           int pt1) {
+  float s = 0.f;
+#pragma unroll 1
+  for (int pt = pt0; pt < pt1; ++pt) {
+    const int tx = pt % a.tiles_w, ty = pt / a.tiles_w % a.tiles_h, tn = pt / a.tiles_w / a.tiles_h;
+#pragma unroll 1
+    for (int p = 0; p < T::BP; ++p) {
+      const int n = tn * T::IMGS + p / (T::TH * T::TW);
+      const int h = ty * T::TH + p / T::TW % T::TH, w = tx * T::TW + p % T::TW;
+      const int hh = h + tap / 3 - 1, ww = w + tap % 3 - 1;
+      if (n >= a.N || h >= a.H || w >= a.W || (unsigned)hh >= (unsigned)a.H ||
+          (unsigned)ww >= (unsigned)a.W)
+        continue;
+      s = fmaf(a.x[(((size_t)n * a.C + c) * a.H + hh) * a.W + ww],
+               a.dy[(((size_t)n * a.K + k) * a.H + h) * a.W + w], s);
+    }
+  }
+  return s;
+}
+
+// VEC: rows are whole aligned quads (W a multiple of 4, 16-byte tensors), so a
+// quad of one channel is one 16-byte load.
+template <class T, bool VEC>
+__global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
+  extern __shared__ u16 ldsu[];
+  float* E = reinterpret_cast<float*>(ldsu);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Blocks in (split, k tile, c tile) order, dealt to the 8 XCDs in contiguous
+  // ranges: the blocks of a split read the same pixel tiles through one L2.
+  int b = blockIdx.x;
+  if (gridDim.x % 8 == 0) b = (b % 8) * (gridDim.x / 8) + b / 8;
+  const int k_tiles = cdiv(a.K, T::BK);
+  const int ct = b % a.c_tiles, kt = b / a.c_tiles % k_tiles, split = b / (a.c_tiles * k_tiles);
+  const int c0 = ct * T::BC, k0 = kt * T::BK;
+  const int pt0 = split * a.tiles_per_split, pt1 = min(a.ptiles, pt0 + a.tiles_per_split);
+  const int nt = pt1 - pt0;
+  const bool do_db = a.db != nullptr && ct == 0;
+  const int HWs = a.H * a.W;
+  const size_t wsz = (size_t)a.K * a.C * 9;
+
+  if (wave >= 4) {
+    // ---- staging waves ----
+    const int ptid = tid - 256;
+    // dy quad: 8 channels doct = ptid / 32, tile pixels 4 (ptid % 32) .. +3.
+    const int doct = ptid >> 5, dp = (ptid & 31) * 4;
+    const int dimg = dp / (T::TH * T::TW), dyy = dp / T::TW % T::TH, dxx = dp % T::TW;
+    const int d_rel = (dimg * a.K + k0 + doct * 8) * HWs + dyy * a.W + dxx;
+    const int d_lds = (doct * T::DPL + dp) * 8;
+    // x quad: lanes from 0 up; x edge pixel: lanes from 255 down.
+    const int qrow = ptid % (T::IMGS * T::HH * (T::TW / 4)) / (T::TW / 4);
+    const int qoct = ptid / (T::IMGS * T::HH * (T::TW / 4));
+    const int qx = ptid % (T::TW / 4) * 4, qimg = qrow / T::HH, qy = qrow % T::HH - 1;
+    const bool q_on = ptid < T::XQ;
+    const int q_rel = (qimg * a.C + c0 + qoct * 8) * HWs + qy * a.W + qx;
+    const int q_lds = T::LDS_DY + (qoct * T::XPL + qrow * T::HW + qx + 1) * 8;
+    const int et = 255 - ptid, erow = et / 2 % (T::IMGS * T::HH);
+    const int eoct = et / (2 * T::IMGS * T::HH), ex = et % 2 ? T::TW : -1;
+    const int eimg = erow / T::HH, ey = erow % T::HH - 1;
+    const bool e_on = et < T::XE;
+    const int e_rel = (eimg * a.C + c0 + eoct * 8) * HWs + ey * a.W + ex;
+    const int e_lds = T::LDS_DY + (eoct * T::XPL + erow * T::HW + ex + 1) * 8;
+    const int dch = min(8, a.K - k0 - doct * 8);           // live channels of each task
+    const int qch = min(8, a.C - c0 - qoct * 8), ech = min(8, a.C - c0 - eoct * 8);
+    f4 rd[8], rq[8];
+    f8v re, dbs = f8v{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // Quad of channel j at byte offset off (+ j planes): its first `cols`
+    // columns are in the image (all or none if VEC).
+    auto quad = [&](rsrc_t r, uint32_t off, int cols, int j) {
+      const int so = j * HWs * 4;
+      if constexpr (VEC) {
+        return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                          r, (int)(cols > 0 ? off : kOOB), so, 0));
+      } else {
+        f4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                               r, (int)(e < cols ? off + 4 * e : kOOB), so, 0));
+        return v;
+      }
+    };
+    auto gload = [&](int t) {
+      const int pt = pt0 + t;
+      const int tx = pt % a.tiles_w, q = pt / a.tiles_w, ty = q % a.tiles_h, tn = q / a.tiles_h;
+      const int n0 = tn * T::IMGS, h0 = ty * T::TH, w0 = tx * T::TW, cnt = min(T::IMGS, a.N - n0);
+      const rsrc_t dr = make_rsrc(a.dy + (size_t)n0 * a.K * HWs, (uint32_t)(cnt * a.K * HWs) * 4u);
+      const rsrc_t xr = make_rsrc(a.x + (size_t)n0 * a.C * HWs, (uint32_t)(cnt * a.C * HWs) * 4u);
+      const int base = h0 * a.W + w0;
+      const int dcol = dimg < cnt && h0 + dyy < a.H ? a.W - w0 - dxx : 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        rd[j] = quad(dr, (uint32_t)(d_rel + base) * 4u, j < dch ? dcol : 0, j);
+      const int qcol = q_on && qimg < cnt && (unsigned)(h0 + qy) < (unsigned)a.H ? a.W - w0 - qx : 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        rq[j] = quad(xr, (uint32_t)(q_rel + base) * 4u, j < qch ? qcol : 0, j);
+      const bool eok = e_on && eimg < cnt && (unsigned)(h0 + ey) < (unsigned)a.H &&
+                       (unsigned)(w0 + ex) < (unsigned)a.W;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        re[j] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(
+                       xr, (int)(eok && j < ech ? (uint32_t)(e_rel + base) * 4u : kOOB),
+                       j * HWs * 4, 0));
+    };
+    auto put = [&](u16* at, int part, f8v v) {
+      const Split8 s = split8(v);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<s8*>(at + p * part) = s.p[p];
+      __builtin_amdgcn_sched_barrier(0);           // one pixel's parts in registers at a time
+    };
+    auto lstore = [&](int buf) {
+      u16* B = ldsu + buf * T::BUF;
+      if (do_db) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dbs[j] += (rd[j][0] + rd[j][1]) + (rd[j][2] + rd[j][3]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        put(B + d_lds + e * 8, T::DPART, f8v{rd[0][e], rd[1][e], rd[2][e], rd[3][e],
+                                             rd[4][e], rd[5][e], rd[6][e], rd[7][e]});
+      if (q_on) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          put(B + q_lds + e * 8, T::XPART, f8v{rq[0][e], rq[1][e], rq[2][e], rq[3][e],
+                                               rq[4][e], rq[5][e], rq[6][e], rq[7][e]});
+      }
+      if (e_on) put(B + e_lds, T::XPART, re);
+    };
+    gload(0);
+    lstore(0);
+    if (nt > 1) gload(1);
+    __syncthreads();
+    for (int t = 0; t < nt; ++t) {
+      if (t + 1 < nt) lstore((t & 1) ^ 1);
+      if (t + 2 < nt) gload(t + 2);
+      __syncthreads();
+    }
+    if (do_db) {
+      // The 32 lanes of a channel group hold its pixels.
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        float v = dbs[j];
+#pragma unroll
+        for (int m = 16; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+        if ((lane & 31) == 0) E[4 * T::COPY + doct * 8 + j] = v;
+      }
+    }
+  } else {
+    // ---- multiplying waves: pixels wave*32 .. +31 of the tile ----
+    const int lr = lane & 15, lq = lane >> 4;
+    // Transpose loads: lane s of a 16-lane group points at channels 4 (s % 4)
+    // .. +3 of the group's pixel s / 4 (second load: of pixel 4 + s / 4).
+    const int ca = lr & 3, pj = wave * 32 + lq * 8 + (lr >> 2);
+    const int d_off = ((ca >> 1) * T::DPL + pj) * 8 + (ca & 1) * 4;
+    const int x_lo = ((ca >> 1) * T::XPL + T::hp(pj)) * 8 + (ca & 1) * 4;
+    const int x_hi = ((ca >> 1) * T::XPL + T::hp(pj + 4)) * 8 + (ca & 1) * 4;
+    f4 acc[4][9], cp[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      cp[i] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 9; ++t) acc[i][t] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    s8 fa[4][3], fb[2][3];
+    __syncthreads();
+    for (int t = 0; t < nt; ++t) {
+      const u16* D = ldsu + (t & 1) * T::BUF;
+      const u16* X = D + T::LDS_DY;
+      auto rd_b = [&](int tap, int s) {
+        const int off = (tap / 3 * T::HW + tap % 3) * 8;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          fb[s][p] = tr8(X + p * T::XPART + x_lo + off, X + p * T::XPART + x_hi + off);
+      };
+      rd_b(0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          const u16* q = D + p * T::DPART + 2 * i * T::DPL * 8 + d_off;
+          fa[i][p] = tr8(q, q + 4 * 8);
+        }
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap) {
+        if (tap < 8) rd_b(tap + 1, (tap + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);         // keep those reads ahead of the MFMAs
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          f4 c = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int m = 0; m < 6; ++m)
+            c = mfma16x16x32(fa[i][kSplitA[m]], fb[tap & 1][kSplitB[m]], c);
+          acc[i][(tap + 8) % 9] += cp[i];          // the tap before
+          cp[i] = c;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i][8] += cp[i];
+    // acc[i][t] element v: row i*16 + 4*lq + v, channel lr, tap t.
+    float* R = E + wave * T::COPY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) R[(i * 16 + 4 * lq + v) * T::RP + lr * 9 + t] = acc[i][t][v];
+  }
+  __syncthreads();
+
+  // ---- the block's 64 k x (16 c x 9 taps), rows contiguous in dw ----
+  float* dst = a.splits == 1 ? a.dw : a.part + (size_t)split * (wsz + a.K);
+  constexpr int QPR = T::BC * 9 / 4;
+  const int cw = min(T::BC, a.C - c0) * 9;           // live columns
+  const bool vec = (a.C * 9) % 4 == 0 && cw % 4 == 0 &&
+                   (((uintptr_t)dst + (size_t)c0 * 9 * sizeof(float)) & 15) == 0;
+#pragma unroll 1
+  for (int q = tid; q < T::BK * QPR; q += 512) {
+    const int row = q / QPR, col = (q % QPR) * 4, k = k0 + row;
+    if (k >= a.K || col >= cw) continue;
+    f4 v = *reinterpret_cast<const f4*>(E + row * T::RP + col);
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f4*>(E + w * T::COPY + row * T::RP + col);
+    if (__builtin_expect(split_suspect(v[0]) || split_suspect(v[1]) || split_suspect(v[2]) ||
+                             split_suspect(v[3]), 0)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (split_suspect(v[e]) && col + e < cw)
+          v[e] = wgrad_one<T>(a, k, c0 + (col + e) / 9, (col + e) % 9, pt0, pt1);
+    }
+    float* o = dst + (size_t)k * a.C * 9 + (size_t)c0 * 9 + col;
+    if (vec) {
+      *reinterpret_cast<f4*>(o) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (col + e < cw) o[e] = v[e];
+    }
+  }
+  if (do_db && tid < T::BK && k0 + tid < a.K)
+    (a.splits == 1 ? a.db : dst + wsz)[k0 + tid] = E[4 * T::COPY + tid];
+}
+
+// ---------------------------------------------------------------- host --
+struct WsPlan {
+  int tile, imgs, tiles_w, tiles_h, ptiles, k_tiles, c_tiles, tps, splits;
+  size_t ws_bytes;
+};
+
+using Ws16 = WsTile<8, 16, 1>;
+using Ws8 = WsTile<8, 8, 2>;
+using Ws4 = WsTile<4, 4, 8>;
+struct WsTileInfo { int th, tw, imgs; const char* name; };
+static const WsTileInfo kWsTiles[] = {{8, 16, 1, "8, 16, 1"}, {8, 8, 2, "8, 8, 2"},
+                                      {4, 4, 8, "4, 4, 8"}};
+
+// The tile that pads the images least (the larger one if equal: less halo),
+// then the split with the least estimated time: a block per CU takes about 5 us
+// for its first tile and its output and 1.8 us a tile; split partials cost
+// their traffic and a launch.  Partials stay within the scratch array of
+// sb_conv3x3_bwd_weight_noalloc, so that call takes every shape this kernel does.
+static WsPlan ws_plan(int N, int C, int H, int W, int K) {
+  WsPlan p{};
+  long least = 0;
+  for (int i = 0; i < 3; ++i) {
+    const WsTileInfo& t = kWsTiles[i];
+    const long n = (long)cdiv(W, t.tw) * cdiv(H, t.th) * cdiv(N, t.imgs);
+    if (i == 0 || n < least) {
+      least = n;
+      p.tile = i;
+      p.imgs = t.imgs;
+      p.tiles_w = cdiv(W, t.tw);
+      p.tiles_h = cdiv(H, t.th);
+    }
+  }
+  p.ptiles = (int)least;
+  p.k_tiles = cdiv(K, 64);
+  p.c_tiles = cdiv(C, 16);
+  const long blocks = (long)p.k_tiles * p.c_tiles;
+  double best = 0;
+  const double dw_mb = (double)K * C * 36e-6;
+  for (int s = 1; s <= 256 && s <= p.ptiles; ++s) {
+    const int tps = cdiv(p.ptiles, s);
+    if (cdiv(p.ptiles, tps) != s) continue;
+    if (s > 1 && (size_t)s * ((size_t)K * C * 9 + K) * sizeof(float) > SB_NOALLOC_SCRATCH_BYTES)
+      break;
+    const double est = (double)cdiv((int)std::min<long>(blocks * s, 1l << 30), 256) *
+                           (5.0 + 1.8 * tps) +
+                       (s > 1 ? 1.5 + dw_mb * (2 * s + 1) / 4.0 : 0.0);
+    if (best == 0 || est < best) {
+      best = est;
+      p.tps = tps;
+      p.splits = s;
+    }
+  }
+  p.ws_bytes = p.splits > 1 ? (size_t)p.splits * ((size_t)K * C * 9 + K) * sizeof(float) : 0;
+  return p;
+}
+
+template <class T, bool VEC>
+static void ws_launch(const WsPlan& p, const WsArgs& a, hipStream_t st) {
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute((const void*)conv3x3_wgrad_split<T, VEC>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
+  });
+  conv3x3_wgrad_split<T, VEC>
+      <<<(unsigned)(p.k_tiles * p.c_tiles * p.splits), 512, T::LDS_BYTES, st>>>(a);
+}
+template <class T>
+static void ws_launch(const WsPlan& p, const WsArgs& a, hipStream_t st) {
+  if (a.W % 4 == 0 && (((uintptr_t)a.x | (uintptr_t)a.dy) & 15) == 0) ws_launch<T, true>(p, a, st);
+  else ws_launch<T, false>(p, a, st);
+}
+
+}  // namespace sb
+
+namespace sbh {
+
+void conv_wgrad_reduce(const float* part, int splits, int K, int C, float* dw, float* db,
+                       hipStream_t st);
+
+// Whether an fp32 weight gradient runs here: at least 8 input channels (the
+// narrow kernels flatten fewer), and images other than 2x2, whose gradient is a
+// dense product without padding (conv3x3_wgrad_2x2).
+bool conv_wgrad_split_takes(int C, int H, int W) {
+  return C >= 8 && W >= 4 && !(H == 2 && W == 2);
+}
+
+size_t conv_wgrad_split_ws(int N, int C, int H, int W, int K) {
+  return sb::ws_plan(N, C, H, W, K).ws_bytes;
+}
+
+int conv_wgrad_split_describe(int N, int C, int H, int W, int K, char* buf, size_t len) {
+  const sb::WsPlan p = sb::ws_plan(N, C, H, W, K);
+  return snprintf(buf, len, "sb::conv3x3_wgrad_split<sb::WsTile<%s>, %s> grid=%dx1x%d",
+                  sb::kWsTiles[p.tile].name, W % 4 == 0 ? "true" : "false", p.k_tiles * p.c_tiles, p.splits);
+}
+
+sb_status conv_wgrad_split(int N, int C, int H, int W, int K, const void* x, const void* dy,
+                           float* dw, float* db, void* ws, size_t ws_bytes, hipStream_t st) {
+  const sb::WsPlan p = sb::ws_plan(N, C, H, W, K);
+  // Buffer ranges: one tile's images of x and of dy.
+  if ((int64_t)std::min(p.imgs, N) * std::max(C, K) * H * W * 4 >= (1ll << 31))
+    return SB_ERR_UNSUPPORTED;
+  if (p.ws_bytes > 0 && (ws == nullptr || ws_bytes < p.ws_bytes)) return SB_ERR_WORKSPACE;
+  sb::WsArgs a{};
+  a.x = (const float*)x; a.dy = (const float*)dy; a.dw = dw; a.db = db;
+  a.part = p.splits > 1 ? (float*)ws : nullptr;
+  a.N = N; a.C = C; a.H = H; a.W = W; a.K = K;
+  a.tiles_w = p.tiles_w; a.tiles_h = p.tiles_h; a.ptiles = p.ptiles;
+  a.tiles_per_split = p.tps; a.c_tiles = p.c_tiles; a.splits = p.splits;
+  switch (p.tile) {
+    case 0: sb::ws_launch<sb::Ws16>(p, a, st); break;
+    case 1: sb::ws_launch<sb::Ws8>(p, a, st); break;
+    default: sb::ws_launch<sb::Ws4>(p, a, st); break;
+  }
+  if (p.splits > 1) conv_wgrad_reduce(a.part, p.splits, K, C, dw, db, st);
+  return launch_status();
+}
+
+}  // namespace sbh
