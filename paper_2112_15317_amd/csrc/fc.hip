@@ -8,15 +8,14 @@
 //             db  = (db +) column sums of G     [ns]
 // with G = dY, or dY * [mask > 0] (ReLU of this shard's output).
 //
-// SB_BF16: x, w_shard, y, dy, the ReLU mask and dx_partial are bfloat16;
-// the kernel widens them exactly to fp32 as it stages them (so the products
-// and sums are the fp32 path's, on the same fp32 MFMA) and rounds y and
-// dx_partial to nearest-even on store; dW and db stay fp32.
-//
-// One fp32 MFMA GEMM kernel (gemm_f32 below) serves the three products;
-// the backward's bias gradient is added up inside the dW product.  Tile
-// shapes and reduction splits are chosen per shape (gemm_plan).
-#include "sb_internal.hpp"
+// One GEMM kernel on the bf16 MFMA (gemm_split below) serves the three
+// products.  fp32 operands are split in three bf16 parts (split_bf16.hpp, six
+// MFMAs per product); bf16 operands are their own first part, so their products
+// are exact with one MFMA, and y and dx_partial are rounded to nearest-even on
+// store.  Sums, dW and db are fp32.  The backward's bias gradient is added up
+// inside the dW product.  Tile shapes and reduction splits are chosen per shape
+// (gemm_plan).
+#include "split_bf16.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -25,60 +24,54 @@
 namespace sb {
 
 // ---------------------------------------------------------------------------
-// GEMM core.  C = epi(A * B) with A [M x K], B [K x N], fp32 accumulation on
-// v_mfma_f32_32x32x2_f32 (one 32x32 output block per instruction).  Block
-// tile BM x BN x 32 (BM, BN in {64, 128}), four waves in a 2 x 2 layout, each
-// owning (BM/2) x (BN/2) as (BM/64) x (BN/64) MFMA blocks.
+// GEMM core.  C = epi(A * B) with A [M x K], B [K x N].  A block of 512 threads
+// has a CU to itself: four waves stage, four multiply (2 x 2, each BM/2 x BN/2
+// as 16 x 16 blocks of the 16x16x32 MFMA).
 //
-// MFMA lane layout (32x32x2, fp32): lane l supplies A[l % 32][k_h] and
-// B[k_h][l % 32] with k_h the half-wave's k (h = l / 32); it receives
-// D[8 (r / 4) + 4 h + r % 4][l % 32] in accumulator element r.
+// A stage is 8*KO of the reduction, kept in LDS as [part][k / 8][row][k % 8] for
+// both operands whatever their layout in memory, so an MFMA operand is one
+// 16-byte read per lane.  A staging lane makes two 16-byte pieces (8 k of a row)
+// of each operand per stage:
+//   * contiguous along k ("K-contiguous"): two pieces of 8 consecutive elements;
+//   * contiguous along its rows: 8 k of two adjacent rows, transposed in
+//     registers.
+// The ReLU mask of dY is applied there.  Out-of-range offsets read 0 (raw buffer
+// loads), so ragged edges need no branches.  Three stages are in LDS: while
+// stage t is multiplied, t + 2 is stored and t + 3 loaded, and t + 1 is already
+// readable, so the operands of the next 32 k are in registers before a stage
+// ends: with two stages each of these short rounds (1536 matrix cycles) would
+// start by waiting for LDS.
 //
-// The reduction runs in chunks of 8 k; MFMA step j (0..3) of a chunk takes
-// k = 4 h + j from half-wave h, for both operands (any fixed pairing of the
-// reduction index gives the same sum up to rounding).  Each operand keeps
-// the layout it has in memory when it is staged in LDS:
-//   * contiguous along k ("K-contiguous"): [row][k], row stride 36 floats;
-//     a lane reads its 4 k of a chunk as one 16-byte read (16-byte units
-//     9 * row + h: the 16 lanes of a read phase hit distinct banks);
-//   * contiguous along its row index: [k][row], k stride BM + 8 floats; a
-//     lane reads one float per step (the two half-waves read rows 4 k apart,
-//     4 (BM + 8) = 32 mod 64 banks: all 64 lanes on distinct banks).
-// Global loads are raw buffer loads whose out-of-range offsets read 0, so
-// ragged edges need no branches around the loads; the ReLU mask of dY is
-// applied when the operand is stored to LDS.  Operands of type E (fp32, or
-// bf16 bits widened exactly) are staged as fp32.
+// A long reduction over few output tiles is split over `splits` ranges of k;
+// each split writes fp32 partials [split][M][N] and gemm_splitk_epilogue sums
+// them in a fixed order.  Blocks are numbered split-major and dealt to the 8
+// XCDs in contiguous ranges of that order, so the blocks one XCD runs share
+// operand slices in its L2.
 //
-// A long reduction over few output tiles is split over `splits` ranges of
-// k; each split writes fp32 partials [split][M][N] and gemm_splitk_epilogue
-// sums them in a fixed order.  Blocks are numbered split-major and dealt to
-// the 8 XCDs in contiguous ranges of that order, so the blocks one XCD runs
-// share operand slices in its L2 (with 8 splits: one split per XCD).
+// colsum (the FC bias gradient): the staging waves of the first row tile's
+// blocks add up the B values they stage.
 //
-// colsum (the FC bias gradient): blocks of the first row tile also add up,
-// on the vector ALU beside the MFMAs, the B values they feed their MFMAs;
-// the two half-waves' sums are combined and the waves of the first row of
-// waves (the other row reads the same B) write the column sums.
-constexpr int GBK = 32;
-constexpr int RK = GBK + 4;                          // [row][k] row stride (floats)
+// Measured (512 x 4096 x 1024 fp32 shard, forward and backward): 132 us with
+// the fp32 MFMA kernels before, 106 like this; the staging waves' loads and
+// vector ALU bound it (dW product 34 us: 25 without the loads, 30 without the
+// splitting, 27 with one MFMA in six).
+constexpr int kGThreads = 512;
 
-template <int R> struct OpGeom {
-  static constexpr int RR = R + 8;                   // [k][row] k stride (floats)
-  static constexpr int KC_FLOATS = R * RK;
-  static constexpr int RC_FLOATS = GBK * RR;
-  static constexpr int GROUPS = R * GBK / 4 / 256;   // 4-element groups per thread
-};
-
-template <int BM, int BN>
+template <int BM_, int BN_, int KO_, int NP_>
 struct GemmTile {
-  static constexpr int OPA = OpGeom<BM>::KC_FLOATS > OpGeom<BM>::RC_FLOATS
-                                 ? OpGeom<BM>::KC_FLOATS : OpGeom<BM>::RC_FLOATS;
-  static constexpr int OPB = OpGeom<BN>::KC_FLOATS > OpGeom<BN>::RC_FLOATS
-                                 ? OpGeom<BN>::KC_FLOATS : OpGeom<BN>::RC_FLOATS;
-  static constexpr int BUF = OPA + OPB;
-  static constexpr size_t LDS_BYTES = 2 * BUF * sizeof(float);
-  static constexpr int RB = BM / 64, CB = BN / 64;   // MFMA blocks per wave
-  static_assert(LDS_BYTES <= 80 * 1024, "two blocks per CU");
+  static constexpr int BM = BM_, BN = BN_, KO = KO_, NP = NP_;
+  static constexpr int RB = BM / 32, CB = BN / 32;          // 16 x 16 blocks per wave
+  static_assert(BM * KO == 512 && BN * KO == 512, "two pieces of each operand per staging lane");
+  // 8-k planes 4 rows apart modulo 16: the planes that neighbouring lanes write
+  // start in different banks.
+  static constexpr int APL = BM + 4, BPL = BN + 4;
+  static constexpr int APART = KO * APL * 8, BPART = KO * BPL * 8;
+  static constexpr int LDS_A = NP * APART, STAGE = LDS_A + NP * BPART;   // bf16
+  static constexpr int EP = BN + 4;                         // output tile row pitch (floats)
+  static constexpr size_t LDS_STAGES = 3 * (size_t)STAGE * sizeof(u16);
+  static constexpr size_t LDS_OUT = ((size_t)BM * EP + BN * KO) * sizeof(float);
+  static constexpr size_t LDS_BYTES = LDS_STAGES > LDS_OUT ? LDS_STAGES : LDS_OUT;
+  static_assert(LDS_BYTES <= 160 * 1024, "one block per CU");
 };
 
 struct GemmArgs {
@@ -93,96 +86,100 @@ struct GemmArgs {
   float* colsum; int colsum_acc;       // column sums of B (k < K), or null
 };
 
-// One operand's staging: R x 32 elements in groups of 4, OpGeom<R>::GROUPS
-// per thread.  K-contiguous: group g = (row g / 8, k quad g % 8), so the 8
-// threads of a row read its 128 contiguous bytes of the tile.
-// Row-contiguous: group g = (row quad g % (R/4), k g / (R/4)).  A thread's
-// groups keep their rows and in-tile k for the whole reduction, so their
-// element offsets (at k = 0) and row checks are worked out once; a tile
-// adds its first k.  VEC loads a group with one vector load (aligned, whole
-// groups in range); otherwise element by element.  The mask (when there is
-// one) is applied when the tile is stored to LDS, so no load waits for
-// another before the store.
-template <int R, bool KC, bool VEC, class E>
-struct Stage {
-  static constexpr int G = OpGeom<R>::GROUPS;
-  f4 v[G], m[G];
-  int off0[G], kin[G];       // element offset at k = 0 (-1: row outside); k in the tile
-  int ld;
-  __device__ __forceinline__ void init(int ld_, int rows, int r0, int tid) {
+// One operand's staging: two pieces of 8 k per lane.  ROWS x 8*KO elements of
+// an operand whose rows start at r0; [kb, ke) the block's range of k.
+template <int ROWS, int KO, int PL, int PART, int NP, bool KC, bool VEC, class E, bool MASK>
+struct GStage {
+  f8v v[2], m[2];
+  int row[2], oct[2];
+  int ld, rows;
+  __device__ __forceinline__ void init(int ld_, int rows_, int r0, int ptid) {
     ld = ld_;
+    rows = rows_;
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-      const int g = tid + i * 256;
-      const int row = KC ? r0 + g / 8 : r0 + (g % (R / 4)) * 4;
-      kin[i] = KC ? (g % 8) * 4 : g / (R / 4);
-      off0[i] = row < rows ? (KC ? row * ld + kin[i] : kin[i] * ld + row) : -1;
+    for (int i = 0; i < 2; ++i) {
+      if (KC) {                                    // piece u: k octet fastest
+        const int u = ptid + 256 * i;
+        oct[i] = u % KO;
+        row[i] = r0 + u / KO;
+      } else {                                     // rows 2p, 2p + 1
+        oct[i] = ptid / (ROWS / 2);
+        row[i] = r0 + ptid % (ROWS / 2) * 2 + i;
+      }
     }
   }
-  __device__ __forceinline__ void load(rsrc_t r, rsrc_t rm, bool masked, int rows, int r0,
-                                       int k0, int ke, int tid) {
+  __device__ __forceinline__ void load_one(rsrc_t r, int k0, int ke, f8v (&d)[2]) {
+    if constexpr (KC) {
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-      const int k = k0 + kin[i];
-      const int koff = KC ? k0 : k0 * ld;
-      if (VEC) {
-        const uint32_t off = (off0[i] >= 0 && k < ke)
-                                 ? (uint32_t)(off0[i] + koff) * (uint32_t)sizeof(E) : kOOB;
-        v[i] = BufLoad<E>::four(r, off);
-        if (masked) m[i] = BufLoad<E>::four(rm, off);
-      } else {
-        const int g = tid + i * 256;
-        const int row = KC ? r0 + g / 8 : r0 + (g % (R / 4)) * 4;
+      for (int i = 0; i < 2; ++i) {
+        const int k = k0 + oct[i] * 8;
+        const uint32_t off = (uint32_t)(row[i] * ld + k) * (uint32_t)sizeof(E);
+        const bool ok = row[i] < rows;
+        if constexpr (VEC) {                       // whole groups of 4
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int rr = KC ? row : row + e, kk = KC ? k + e : k;
-          const bool ok = rr < rows && kk < ke;
-          const uint32_t off =
-              ok ? (uint32_t)(KC ? rr * ld + kk : kk * ld + rr) * (uint32_t)sizeof(E) : kOOB;
-          v[i][e] = BufLoad<E>::one(r, off);
-          if (masked) m[i][e] = BufLoad<E>::one(rm, off);
+          for (int q = 0; q < 2; ++q) {
+            const f4 t = BufLoad<E>::four(r, ok && k + 4 * q < ke ? off + 4 * q * sizeof(E) : kOOB);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d[i][4 * q + e] = t[e];
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            d[i][e] = BufLoad<E>::one(r, ok && k + e < ke ? off + e * sizeof(E) : kOOB);
+        }
+      }
+    } else {
+      const int k = k0 + oct[0] * 8;
+      const uint32_t off = (uint32_t)(k * ld + row[0]) * (uint32_t)sizeof(E);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t o = off + (uint32_t)(e * ld) * (uint32_t)sizeof(E);
+        const bool ok = k + e < ke;
+        if constexpr (VEC && sizeof(E) == 4) {     // both rows or neither
+          typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+          const u2 t = __builtin_bit_cast(
+              u2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)(ok && row[0] < rows ? o : kOOB), 0, 0));
+          d[0][e] = __uint_as_float(t[0]);
+          d[1][e] = __uint_as_float(t[1]);
+        } else if constexpr (VEC) {
+          const uint32_t t =
+              __builtin_amdgcn_raw_buffer_load_b32(r, (int)(ok && row[0] < rows ? o : kOOB), 0, 0);
+          d[0][e] = __uint_as_float(t << 16);
+          d[1][e] = __uint_as_float(t & 0xffff0000u);
+        } else {
+          d[0][e] = BufLoad<E>::one(r, ok && row[0] < rows ? o : kOOB);
+          d[1][e] = BufLoad<E>::one(r, ok && row[1] < rows ? o + (uint32_t)sizeof(E) : kOOB);
         }
       }
     }
   }
-  __device__ __forceinline__ void store(float* S, bool masked, int tid) const {
+  __device__ __forceinline__ void load(rsrc_t r, rsrc_t rm, int k0, int ke) {
+    load_one(r, k0, ke, v);
+    if constexpr (MASK) load_one(rm, k0, ke, m);
+  }
+  // Stores the pieces; r0 as in init.  Returns the (masked) values in v.
+  __device__ __forceinline__ void store(u16* S, int r0) {
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-      const int g = tid + i * 256;
-      float* p = KC ? S + (g / 8) * RK + (g % 8) * 4 : S + (g / (R / 4)) * OpGeom<R>::RR +
-                                                         (g % (R / 4)) * 4;
-      f4 x = v[i];
-      if (masked) {
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (MASK) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = m[i][e] > 0.f ? x[e] : 0.f;
+        for (int e = 0; e < 8; ++e) v[i][e] = m[i][e] > 0.f ? v[i][e] : 0.f;
       }
-      *reinterpret_cast<f4*>(p) = x;
+      u16* at = S + (oct[i] * PL + row[i] - r0) * 8;
+      if constexpr (NP == 1) {                     // bf16 values: exact
+        u32x4 h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = f32x2_to_bf16x2(v[i][2 * e], v[i][2 * e + 1]);
+        *reinterpret_cast<s8*>(at) = __builtin_bit_cast(s8, h);
+      } else {
+        const Split8 s = split8(v[i]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<s8*>(at + p * PART) = s.p[p];
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 };
-
-// Operand values of chunk c (8 k) for NB 32-row blocks of a wave:
-// f[blk][j] = element (row row0 + 32 blk + l % 32, k = 8 c + 4 h + j).
-template <int R, bool KC, int NB>
-__device__ __forceinline__ void frag32(const float* S, int row0, int c, int h, int l32,
-                                       f4 (&f)[NB]) {
-#pragma unroll
-  for (int blk = 0; blk < NB; ++blk) {
-    const int row = row0 + blk * 32 + l32;
-    if (KC) {
-      f[blk] = *reinterpret_cast<const f4*>(S + row * RK + c * 8 + h * 4);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) f[blk][j] = S[(c * 8 + h * 4 + j) * OpGeom<R>::RR + row];
-    }
-  }
-}
-
-typedef float f16v __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ f16v mfma32x32x2(float a, float b, f16v c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
 
 // The block's (row tile, column tile, split) from its linear id: dealt to
 // the 8 XCDs in contiguous ranges of the split-major order when the grid is
@@ -198,164 +195,264 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& g, int& mtile, int& n
   ntile = t - mtile * g.nt;
 }
 
-template <int BM, int BN, bool A_KC, bool B_KC, bool VEC, class E, class CE, bool AMK, bool BMK>
-__global__ __launch_bounds__(256, 2) void gemm_f32(GemmArgs g) {
-  using T = GemmTile<BM, BN>;
-  extern __shared__ float lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  const int h = lane >> 5, l32 = lane & 31;
+// One output in plain fp32, over k in [k0, k1).
+template <bool A_KC, bool B_KC, class E>
+__device__ __forceinline__ float gemm_one(const GemmArgs& g, int m, int n, int k0, int k1) {
+  float s = 0.f;
+#pragma unroll 1
+  for (int k = k0; k < k1; ++k) {
+    const size_t ao = A_KC ? (size_t)m * g.lda + k : (size_t)k * g.lda + m;
+    const size_t bo = B_KC ? (size_t)n * g.ldb + k : (size_t)k * g.ldb + n;
+    float av = Elem<E>::load((const E*)g.a, ao), bv = Elem<E>::load((const E*)g.b, bo);
+    if (g.amask && !(Elem<E>::load((const E*)g.amask, ao) > 0.f)) av = 0.f;
+    if (g.bmask && !(Elem<E>::load((const E*)g.bmask, bo) > 0.f)) bv = 0.f;
+    s = fmaf(av, bv, s);
+  }
+  return s;
+}
+
+template <class T, bool A_KC, bool B_KC, bool VEC, class E, class CE, bool AMK, bool BMK>
+__global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
+  extern __shared__ u16 ldsu[];
+  float* O = reinterpret_cast<float*>(ldsu);
+  constexpr int KS = T::KO * 8;                    // k per stage
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int mtile, ntile, split;
   gemm_block(g, mtile, ntile, split);
-  const int m0 = mtile * BM, n0 = ntile * BN;
+  const int m0 = mtile * T::BM, n0 = ntile * T::BN;
   const int kb = split * g.k_per_split;
   const int ke = min(g.K, kb + g.k_per_split);
-  // Whole operand tensors (the host keeps them below 2^31 bytes).
-  const size_t a_elems = A_KC ? (size_t)(g.M - 1) * g.lda + g.K : (size_t)(g.K - 1) * g.lda + g.M;
-  const size_t b_elems = B_KC ? (size_t)(g.N - 1) * g.ldb + g.K : (size_t)(g.K - 1) * g.ldb + g.N;
-  const rsrc_t ra = make_rsrc(g.a, (uint32_t)(a_elems * sizeof(E)));
-  const rsrc_t rb = make_rsrc(g.b, (uint32_t)(b_elems * sizeof(E)));
-  const rsrc_t ram = make_rsrc(g.amask ? g.amask : g.a, (uint32_t)(a_elems * sizeof(E)));
-  const rsrc_t rbm = make_rsrc(g.bmask ? g.bmask : g.b, (uint32_t)(b_elems * sizeof(E)));
-  constexpr bool amasked = AMK, bmasked = BMK;
+  const int nk = ke > kb ? cdiv(ke - kb, KS) : 0;
   const bool do_colsum = g.colsum != nullptr && mtile == 0;
 
-  f16v acc[T::RB][T::CB];
+  if (wave >= 4) {
+    // ---- staging waves ----
+    const int ptid = tid - 256;
+    // Whole operand tensors (the host keeps them below 2^31 bytes).
+    const size_t a_elems = A_KC ? (size_t)(g.M - 1) * g.lda + g.K : (size_t)(g.K - 1) * g.lda + g.M;
+    const size_t b_elems = B_KC ? (size_t)(g.N - 1) * g.ldb + g.K : (size_t)(g.K - 1) * g.ldb + g.N;
+    const rsrc_t ra = make_rsrc(g.a, (uint32_t)(a_elems * sizeof(E)));
+    const rsrc_t rb = make_rsrc(g.b, (uint32_t)(b_elems * sizeof(E)));
+    const rsrc_t ram = make_rsrc(AMK ? g.amask : g.a, (uint32_t)(a_elems * sizeof(E)));
+    const rsrc_t rbm = make_rsrc(BMK ? g.bmask : g.b, (uint32_t)(b_elems * sizeof(E)));
+    GStage<T::BM, T::KO, T::APL, T::APART, T::NP, A_KC, VEC, E, AMK> sa;
+    GStage<T::BN, T::KO, T::BPL, T::BPART, T::NP, B_KC, VEC, E, BMK> sb_;
+    sa.init(g.lda, g.M, m0, ptid);
+    sb_.init(g.ldb, g.N, n0, ptid);
+    float cs[2] = {0.f, 0.f};                      // column sums of this lane's two rows of B
+    auto add_cols = [&](const auto& q) {
 #pragma unroll
-  for (int i = 0; i < T::RB; ++i)
-#pragma unroll
-    for (int j = 0; j < T::CB; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  float csum[T::CB];
-#pragma unroll
-  for (int j = 0; j < T::CB; ++j) csum[j] = 0.f;
-
-  Stage<BM, A_KC, VEC, E> sa[2];
-  Stage<BN, B_KC, VEC, E> sb_[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    sa[q].init(g.lda, g.M, m0, tid);
-    sb_[q].init(g.ldb, g.N, n0, tid);
-  }
-  auto Abuf = [&](int b) { return lds + b * T::BUF; };
-  auto Bbuf = [&](int b) { return lds + b * T::BUF + T::OPA; };
-
-  const int nk = ke > kb ? cdiv(ke - kb, GBK) : 0;
-  sa[0].load(ra, ram, amasked, g.M, m0, kb, ke, tid);
-  sb_[0].load(rb, rbm, bmasked, g.N, n0, kb, ke, tid);
-  sa[1].load(ra, ram, amasked, g.M, m0, kb + GBK, ke, tid);
-  sb_[1].load(rb, rbm, bmasked, g.N, n0, kb + GBK, ke, tid);
-  sa[0].store(Abuf(0), amasked, tid);
-  sb_[0].store(Bbuf(0), bmasked, tid);
-  sa[0].load(ra, ram, amasked, g.M, m0, kb + 2 * GBK, ke, tid);
-  sb_[0].load(rb, rbm, bmasked, g.N, n0, kb + 2 * GBK, ke, tid);
-  __syncthreads();
-  // Tile j's operands travel in register set j % 2.  Per tile t: the first
-  // chunk's operands are read from LDS, tile t + 1 is stored to the other
-  // LDS buffer and tile t + 3 is requested into the register set that store
-  // frees (two tiles ahead of its own store); then each chunk's MFMAs run
-  // while the following chunk's operands are read.
-  auto step = [&](auto P, int t) {
-    constexpr int Q = decltype(P)::value;          // t % 2
-    const int buf = Q;
-    const float* A = Abuf(buf);
-    const float* B = Bbuf(buf);
-    f4 fa[T::RB], fb[T::CB], na[T::RB], nb[T::CB];
-    frag32<BM, A_KC, T::RB>(A, wm * (BM / 2), 0, h, l32, fa);
-    frag32<BN, B_KC, T::CB>(B, wn * (BN / 2), 0, h, l32, fb);
-    // Unconditional: a tile past the end loads as zeros (every offset out
-    // of range) and its LDS copy is never read, so the loop body has one
-    // path and the compiler counts outstanding loads exactly.
-    sa[Q ^ 1].store(Abuf(buf ^ 1), amasked, tid);
-    sb_[Q ^ 1].store(Bbuf(buf ^ 1), bmasked, tid);
-    sa[Q ^ 1].load(ra, ram, amasked, g.M, m0, kb + (t + 3) * GBK, ke, tid);
-    sb_[Q ^ 1].load(rb, rbm, bmasked, g.N, n0, kb + (t + 3) * GBK, ke, tid);
-#pragma unroll
-    for (int c = 0; c < GBK / 8; ++c) {
-      if (c + 1 < GBK / 8) {
-        frag32<BM, A_KC, T::RB>(A, wm * (BM / 2), c + 1, h, l32, na);
-        frag32<BN, B_KC, T::CB>(B, wn * (BN / 2), c + 1, h, l32, nb);
-      }
-      // Keep those reads ahead of this chunk's MFMAs (the scheduler would
-      // otherwise sink them next to their first use).
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < T::RB; ++i)
-#pragma unroll
-          for (int n = 0; n < T::CB; ++n) acc[i][n] = mfma32x32x2(fa[i][j], fb[n][j], acc[i][n]);
-      if (do_colsum) {
-#pragma unroll
-        for (int n = 0; n < T::CB; ++n) csum[n] += (fb[n][0] + fb[n][1]) + (fb[n][2] + fb[n][3]);
-      }
-      if (c + 1 < GBK / 8) {
-#pragma unroll
-        for (int i = 0; i < T::RB; ++i) fa[i] = na[i];
-#pragma unroll
-        for (int n = 0; n < T::CB; ++n) fb[n] = nb[n];
-      }
+      for (int i = 0; i < 2; ++i)
+        cs[i] += ((q.v[i][0] + q.v[i][1]) + (q.v[i][2] + q.v[i][3])) +
+                 ((q.v[i][4] + q.v[i][5]) + (q.v[i][6] + q.v[i][7]));
+    };
+    auto load = [&](int t) {                       // a stage past the end loads zeros
+      sa.load(ra, ram, kb + t * KS, ke);
+      sb_.load(rb, rbm, kb + t * KS, ke);
+    };
+    auto store = [&](int t) {
+      u16* S = ldsu + t % 3 * T::STAGE;
+      sa.store(S, m0);
+      sb_.store(S + T::LDS_A, n0);
+      if (!B_KC && do_colsum) add_cols(sb_);
+    };
+    if (nk > 1) {                                  // both loads in flight at once
+      GStage<T::BM, T::KO, T::APL, T::APART, T::NP, A_KC, VEC, E, AMK> sa0 = sa;
+      GStage<T::BN, T::KO, T::BPL, T::BPART, T::NP, B_KC, VEC, E, BMK> sb0 = sb_;
+      sa0.load(ra, ram, kb, ke);
+      sb0.load(rb, rbm, kb, ke);
+      load(1);
+      sa0.store(ldsu, m0);
+      sb0.store(ldsu + T::LDS_A, n0);
+      if (!B_KC && do_colsum) add_cols(sb0);
+      store(1);
+    } else {
+      load(0);
+      store(0);
     }
+    if (nk > 2) load(2);
     __syncthreads();
-  };
-  int t = 0;
-  for (; t + 1 < nk; t += 2) {
-    step(std::integral_constant<int, 0>{}, t);
-    step(std::integral_constant<int, 1>{}, t + 1);
-  }
-  if (t < nk) step(std::integral_constant<int, 0>{}, t);
-
-  if (do_colsum) {
-#pragma unroll
-    for (int n = 0; n < T::CB; ++n) {
-      const float s = csum[n] + __shfl_xor(csum[n], 32, 64);
-      const int col = n0 + wn * (BN / 2) + n * 32 + l32;
-      if (wm == 0 && h == 0 && col < g.N)
-        g.colsum[col] = g.colsum_acc ? g.colsum[col] + s : s;
+    for (int t = 0; t < nk; ++t) {
+      if (t + 2 < nk) store(t + 2);
+      if (t + 3 < nk) load(t + 3);
+      __syncthreads();
     }
-  }
-
-  // acc[i][n] element r holds C[m0 + wm*BM/2 + 32 i + 8 (r/4) + 4 h + r%4]
-  //                            [n0 + wn*BN/2 + 32 n + l32].
-  const bool partial = g.splits > 1;
-  float* part = partial ? (float*)g.c + (size_t)split * g.M * g.ldc : nullptr;
-  CE* dst = (CE*)g.c;
+    if (!B_KC && do_colsum) {                      // [octet][row] after the output tile
 #pragma unroll
-  for (int n = 0; n < T::CB; ++n) {
-    const int col = n0 + wn * (BN / 2) + n * 32 + l32;
-    if (col >= g.N) continue;
-    const float bv = (!partial && g.bias) ? g.bias[col] : 0.f;
+      for (int i = 0; i < 2; ++i) O[T::BM * T::EP + sb_.oct[i] * T::BN + sb_.row[i] - n0] = cs[i];
+    }
+  } else {
+    // ---- multiplying waves ----
+    const int lr = lane & 15, lq = lane >> 4;
+    const int wm = wave & 1, wn = wave >> 1;
+    const int a_off = (lq * T::APL + wm * (T::BM / 2) + lr) * 8;
+    const int b_off = T::LDS_A + (lq * T::BPL + wn * (T::BN / 2) + lr) * 8;
+    f4 acc[T::RB][T::CB], cp[T::RB];
+#pragma unroll
+    for (int i = 0; i < T::RB; ++i) {
+      cp[i] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < T::CB; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    s8 fa[2][T::RB][T::NP], fb[2][T::NP];
+    auto rd_a = [&](const u16* S, int step, int s) {
+#pragma unroll
+      for (int i = 0; i < T::RB; ++i)
+#pragma unroll
+        for (int p = 0; p < T::NP; ++p)
+          fa[s][i][p] = *reinterpret_cast<const s8*>(S + a_off + p * T::APART +
+                                                     (step * 4 * T::APL + i * 16) * 8);
+    };
+    auto rd_b = [&](const u16* S, int step, int j, int s) {
+#pragma unroll
+      for (int p = 0; p < T::NP; ++p)
+        fb[s][p] = *reinterpret_cast<const s8*>(S + b_off + p * T::BPART +
+                                                (step * 4 * T::BPL + j * 16) * 8);
+    };
+    constexpr int STEPS = T::KO / 4;               // 32-k steps per stage
+    static_assert(T::CB % 2 == 0, "column blocks alternate two register sets");
+    // One 32-k step out of register set P, the next step's operands read
+    // meanwhile (from S2 if it is in the next stage).
+    auto step = [&](auto P, const u16* S, const u16* S2, int q, int q2) {
+      constexpr int s = decltype(P)::value;
+      rd_a(S2, q2, s ^ 1);
+#pragma unroll
+      for (int j = 0; j < T::CB; ++j) {
+        if (j + 1 < T::CB) rd_b(S, q, j + 1, (j + 1) & 1);
+        else rd_b(S2, q2, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);         // keep those reads ahead of the MFMAs
+#pragma unroll
+        for (int i = 0; i < T::RB; ++i) {
+          if constexpr (T::NP == 1) {
+            acc[i][j] = mfma16x16x32(fa[s][i][0], fb[j & 1][0], acc[i][j]);
+          } else {
+            f4 c = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int m = 0; m < 6; ++m)
+              c = mfma16x16x32(fa[s][i][kSplitA[m]], fb[j & 1][kSplitB[m]], c);
+            acc[i][(j + T::CB - 1) % T::CB] += cp[i];   // the block before
+            cp[i] = c;
+          }
+        }
+        if constexpr (T::NP == 3) {
+#pragma unroll
+          for (int r = 0; r < 2 * T::RB; ++r) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    __syncthreads();
+    rd_a(ldsu, 0, 0);
+    rd_b(ldsu, 0, 0, 0);
+    auto stage = [&](auto P, int t) {
+      constexpr int s0 = decltype(P)::value;
+      const u16* S = ldsu + t % 3 * T::STAGE;
+      const u16* S2 = ldsu + (t + 1) % 3 * T::STAGE;   // past the end: stale, unused
+      if constexpr (STEPS == 1) {
+        step(std::integral_constant<int, s0>{}, S, S2, 0, 0);
+      } else {
+        static_assert(STEPS == 1 || STEPS == 2, "one or two steps per stage");
+        step(std::integral_constant<int, s0>{}, S, S, 0, 1);
+        step(std::integral_constant<int, s0 ^ 1>{}, S, S2, 1, 0);
+      }
+      __syncthreads();
+    };
+    int t = 0;
+    for (; t + 1 < nk; t += 2) {
+      stage(std::integral_constant<int, 0>{}, t);
+      stage(std::integral_constant<int, STEPS & 1>{}, t + 1);
+    }
+    if (t < nk) stage(std::integral_constant<int, 0>{}, t);
+#pragma unroll
+    for (int i = 0; i < T::RB; ++i) acc[i][T::CB - 1] += cp[i];
+    // acc[i][j] element v: row wm*BM/2 + 16 i + 4 lq + v, column wn*BN/2 + 16 j + lr.
 #pragma unroll
     for (int i = 0; i < T::RB; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (m >= g.M) continue;
-        float v = acc[i][n][r];
-        const size_t o = (size_t)m * g.ldc + col;
-        if (partial) {
-          part[o] = v;
-          continue;
-        }
-        v += bv;
-        if (g.relu && !(v > 0.f)) v = 0.f;
-        if (g.accumulate) v += Elem<CE>::load(dst, o);
-        Elem<CE>::store(dst, o, v);
+      for (int j = 0; j < T::CB; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          O[(wm * (T::BM / 2) + 16 * i + 4 * lq + v) * T::EP + wn * (T::BN / 2) + 16 * j + lr] =
+              acc[i][j][v];
+  }
+  __syncthreads();
+
+  if (do_colsum && tid < T::BN && n0 + tid < g.N) {
+    float s = 0.f;
+#pragma unroll
+    for (int o = 0; o < T::KO; ++o) s += O[T::BM * T::EP + o * T::BN + tid];
+    float* cs = g.colsum + (g.splits > 1 ? (size_t)split * g.N : 0);   // this split's partials
+    cs[n0 + tid] = g.colsum_acc ? cs[n0 + tid] + s : s;
+  }
+  const bool partial = g.splits > 1;
+  float* part = partial ? (float*)g.c + (size_t)split * g.M * g.ldc : nullptr;
+  CE* dst = (CE*)g.c;
+  const bool vec4 = g.N % 4 == 0 && g.ldc % 4 == 0 &&
+                    ((uintptr_t)(partial ? (void*)part : g.c) &
+                     (partial ? 15 : 4 * sizeof(CE) - 1)) == 0;
+#pragma unroll 1
+  for (int q = tid; q < T::BM * T::BN / 4; q += kGThreads) {
+    const int r = q / (T::BN / 4), c = q % (T::BN / 4) * 4;
+    const int m = m0 + r, n = n0 + c;
+    if (m >= g.M || n >= g.N) continue;
+    f4 v = *reinterpret_cast<const f4*>(O + r * T::EP + c);
+    if (__builtin_expect(split_suspect(v[0]) || split_suspect(v[1]) || split_suspect(v[2]) ||
+                             split_suspect(v[3]), 0)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (split_suspect(v[e]) && n + e < g.N) v[e] = gemm_one<A_KC, B_KC, E>(g, m, n + e, kb, ke);
+    }
+    const size_t o = (size_t)m * g.ldc + n;
+    if (!partial) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (g.bias && n + e < g.N) v[e] += g.bias[n + e];
+        if (g.relu && !(v[e] > 0.f)) v[e] = 0.f;
       }
+    }
+    if (vec4) {
+      if (partial) {
+        *reinterpret_cast<f4*>(part + o) = v;
+      } else {
+        if (g.accumulate) v += Elem<CE>::load4(dst + o);
+        Elem<CE>::store4(dst + o, v);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (n + e >= g.N) continue;
+        if (partial) part[o + e] = v[e];
+        else Elem<CE>::store(dst, o + e, g.accumulate ? v[e] + Elem<CE>::load(dst, o + e) : v[e]);
+      }
+    }
   }
 }
 
 // out[m, n] = epi(sum_s part[s][m][n]): + bias[n], ReLU, + out (accumulate),
 // rounded to the output type CE.  Four consecutive outputs per thread when
-// N is a multiple of 4 (the splits summed in order for each of them).
+// N is a multiple of 4 (the splits summed in order for each of them).  The
+// blocks past the output add up the splits' column sums csum [splits][N] (db).
 template <class CE>
 __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
     const float* __restrict__ part, int splits, int M, int N, CE* __restrict__ out, int ldo,
-    const float* __restrict__ bias, int relu, int accumulate) {
-  const size_t i4 = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i4 >= (size_t)M * N) return;
+    const float* __restrict__ bias, int relu, int accumulate, const float* __restrict__ csum,
+    float* __restrict__ db, int db_accumulate) {
   const size_t stride = (size_t)M * N;
+  const size_t blocks = (stride + 1023) / 1024;
+  if (blockIdx.x >= blocks) {
+    const int n = (int)(blockIdx.x - blocks) * 256 + threadIdx.x;
+    if (n >= N) return;
+    float v = 0.f;
+    for (int s = 0; s < splits; ++s) v += csum[(size_t)s * N + n];
+    db[n] = db_accumulate ? db[n] + v : v;
+    return;
+  }
+  const size_t i4 = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i4 >= stride) return;
   if (N % 4 == 0) {
     const f4 v = split_sum4(part, splits, stride, i4);
     const int m = (int)(i4 / N), n = (int)(i4 - (size_t)m * N);
@@ -372,10 +469,18 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
   }
   for (int e = 0; e < 4; ++e) {
     const size_t i = i4 + e;
-    if (i >= (size_t)M * N) return;
+    if (i >= stride) return;
     const int m = (int)(i / N), n = (int)(i - (size_t)m * N);
     float x = 0.f;
-    for (int s = 0; s < splits; ++s) x += part[(size_t)s * stride + i];
+    int s = 0;
+    for (; s + 8 <= splits; s += 8) {              // eight loads in flight
+      float p[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) p[q] = part[(size_t)(s + q) * stride + i];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x += p[q];
+    }
+    for (; s < splits; ++s) x += part[(size_t)s * stride + i];
     if (bias) x += bias[n];
     if (relu && !(x > 0.f)) x = 0.f;
     const size_t o = (size_t)m * ldo + n;
@@ -384,92 +489,61 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
   }
 }
 
-// db[j] = (db[j] +) sum_i G[i][j], for the plans whose GEMM cannot add the
-// column sums itself (a split reduction).  A block owns 64 columns; its 16
-// waves sum every 16th row (four independent partial sums each, combined in
-// a fixed order), then the wave sums are added in order through LDS.
-template <class E>
-__global__ __launch_bounds__(1024) void col_sum(const E* __restrict__ dy,
-                                                const E* __restrict__ mask, int M, int N,
-                                                int ld, float* __restrict__ db, int accumulate) {
-  __shared__ float part[16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
-  float s4[4] = {0.f, 0.f, 0.f, 0.f};
-  if (j < N) {
-    int u = 0;
-    for (int i = wave; i < M; i += 16, u = (u + 1) & 3) {
-      const size_t o = (size_t)i * ld + j;
-      float v = Elem<E>::load(dy, o);
-      if (mask && !(Elem<E>::load(mask, o) > 0.f)) v = 0.f;
-      s4[u] += v;
-    }
-  }
-  part[wave][lane] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-  __syncthreads();
-  if (wave != 0 || j >= N) return;
-  float v = 0.f;
-#pragma unroll
-  for (int w = 0; w < 16; ++w) v += part[w][lane];
-  db[j] = accumulate ? db[j] + v : v;
-}
+// Tile shape and split of one GEMM: the least estimated time over 128x128 and
+// 64x64 block tiles and 1 to 32 ranges of k.  A block per CU takes about 4 us
+// for its first stages and its output; per 32 k a 128x128 tile takes 0.9 us and
+// a 64x64 tile, a fourth of the products on the same staging, 0.4 (bf16: 0.3 and
+// 0.2, the staging); partials cost their traffic and a launch.
+struct GemmPlan { int bm, mt, nt, splits, kps; size_t ws_bytes; };
 
-// Tile shape and split of one GEMM.  Candidates: 128x128, 128x64 and 64x64
-// block tiles, 1..16 splits of the reduction (each at least 4 k-tiles).
-// Measured on the FC shard's shapes, a block alone on its CU waits on its
-// operand loads, while two blocks per CU hide each other's waits, and
-// splits cost their partials and a reduction launch.  So the plan takes the
-// most blocks up to 512 (two per CU), then the fewest splits, then the
-// largest tile.
-struct GemmPlan { int bm, bn, mt, nt, splits, kps; size_t ws_bytes; };
-
-static GemmPlan gemm_plan(int M, int N, int K, int /*esize*/) {
-  static const int kTiles[3][2] = {{128, 128}, {128, 64}, {64, 64}};
+static GemmPlan gemm_plan(int M, int N, int K, int esize) {
   GemmPlan best{};
-  long best_blocks = 0;
-  const int ktiles = cdiv(K, GBK);
-  for (const auto& t : kTiles) {
-    const int mt = cdiv(M, t[0]), nt = cdiv(N, t[1]);
-    for (int s = 1; s <= 16; s *= 2) {
-      if (s > 1 && ktiles / s < 4) break;
+  double best_t = 0;
+  for (int bm : {128, 64}) {
+    const int ks = bm == 128 ? 32 : 64;                     // k per stage
+    const double t32 = esize == 2 ? (bm == 128 ? 0.3 : 0.2) : (bm == 128 ? 0.9 : 0.4);
+    const int mt = cdiv(M, bm), nt = cdiv(N, bm), ktiles = cdiv(K, ks);
+    for (int s = 1; s <= 32 && s <= ktiles; ++s) {
       const int tps = cdiv(ktiles, s);
-      const int splits = cdiv(ktiles, tps);
-      if (splits != s) continue;
-      const long blocks = std::min<long>((long)mt * nt * splits, 512);
-      const bool better = best.mt == 0 || blocks > best_blocks ||
-                          (blocks == best_blocks && splits < best.splits);
-      if (better) {
-        best = GemmPlan{t[0], t[1], mt, nt, splits, tps * GBK, 0};
-        best_blocks = blocks;
+      if (cdiv(ktiles, tps) != s) continue;
+      const double est = (double)cdiv((int)std::min<long>((long)mt * nt * s, 1l << 30), 256) *
+                             (4.0 + t32 * tps * ks / 32) +
+                         (s > 1 ? 2.0 + (double)M * N * 4e-6 * (2 * s + 1) / 4.0 : 0.0);
+      if (best_t == 0 || est < best_t) {
+        best_t = est;
+        best = GemmPlan{bm, mt, nt, s, tps * ks, 0};
       }
     }
   }
-  best.ws_bytes = best.splits > 1 ? (size_t)best.splits * M * N * sizeof(float) : 0;
+  // Each split's output, then each split's column sums (db of the dW product).
+  best.ws_bytes = best.splits > 1 ? (size_t)best.splits * ((size_t)M * N + N) * sizeof(float) : 0;
   return best;
 }
 
-// 4-element groups load as one vector (16 bytes fp32, 8 bytes bf16).
+// Vector staging: K-contiguous operands in groups of 4 elements along k,
+// row-contiguous ones in pairs of rows.
 template <class E>
-static bool vec_ok(const void* p, int ld, int contiguous_extent) {
-  return ((uintptr_t)p & (4 * sizeof(E) - 1)) == 0 && ld % 4 == 0 && contiguous_extent % 4 == 0;
+static bool vec_ok(const void* p, int ld, int contiguous_extent, bool kc) {
+  const int n = kc ? 4 : 2;
+  return ((uintptr_t)p & (n * sizeof(E) - 1)) == 0 && ld % n == 0 && contiguous_extent % n == 0;
 }
 
-template <int BM, int BN, bool AK, bool BK, bool VEC, class E, class CE, bool AMK, bool BMK>
+template <class T, bool AK, bool BK, bool VEC, class E, class CE, bool AMK, bool BMK>
 static void gemm_launch_t(const GemmPlan& p, const GemmArgs& g, hipStream_t st) {
-  using T = GemmTile<BM, BN>;
   static std::once_flag once;
   std::call_once(once, [] {
-    (void)hipFuncSetAttribute((const void*)gemm_f32<BM, BN, AK, BK, VEC, E, CE, AMK, BMK>,
+    (void)hipFuncSetAttribute((const void*)gemm_split<T, AK, BK, VEC, E, CE, AMK, BMK>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
   });
-  gemm_f32<BM, BN, AK, BK, VEC, E, CE, AMK, BMK><<<p.mt * p.nt * p.splits, 256, T::LDS_BYTES, st>>>(g);
+  gemm_split<T, AK, BK, VEC, E, CE, AMK, BMK>
+      <<<(unsigned)(p.mt * p.nt * p.splits), kGThreads, T::LDS_BYTES, st>>>(g);
 }
 
 template <bool AK, bool BK, bool VEC, class E, class CE, bool AMK, bool BMK>
 static void gemm_launch_m(const GemmPlan& p, const GemmArgs& g, hipStream_t st) {
-  if (p.bm == 128 && p.bn == 128) gemm_launch_t<128, 128, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
-  else if (p.bm == 128) gemm_launch_t<128, 64, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
-  else gemm_launch_t<64, 64, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+  constexpr int NP = sizeof(E) == 2 ? 1 : 3;
+  if (p.bm == 128) gemm_launch_t<GemmTile<128, 128, 4, NP>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+  else gemm_launch_t<GemmTile<64, 64, 8, NP>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
 }
 
 // The masks are template arguments, so that no load or store of the
@@ -490,11 +564,9 @@ static void gemm_launch(const GemmPlan& p, const GemmArgs& g, hipStream_t st) {
 // C (ldc) = epi(A * B): the GEMM applies the epilogue itself when the
 // reduction is not split; otherwise it writes per-split partial sums to the
 // workspace and gemm_splitk_epilogue adds them in order and applies it.
-// colsum (may be null): column sums of B, added by the GEMM when it is not
-// split, else by col_sum from (csrc, cmask, cld).
+// colsum (may be null): column sums of B, likewise.
 template <bool AK, bool BK, class E, class CE>
-static sb_status gemm_run(GemmArgs g, float* ws, size_t ws_bytes, hipStream_t st,
-                          const E* csrc = nullptr, const E* cmask = nullptr, int cld = 0) {
+static sb_status gemm_run(GemmArgs g, float* ws, size_t ws_bytes, hipStream_t st) {
   // Masks exist only where gemm_launch instantiates them.
   if ((g.amask && !(AK && BK)) || (g.bmask && (AK || BK))) return SB_ERR_UNSUPPORTED;
   GemmPlan p = gemm_plan(g.M, g.N, g.K, (int)sizeof(E));
@@ -505,10 +577,10 @@ static sb_status gemm_run(GemmArgs g, float* ws, size_t ws_bytes, hipStream_t st
   const int64_t es = (int64_t)sizeof(E);
   if (a_elems * es >= (1ll << 31) || b_elems * es >= (1ll << 31)) return SB_ERR_UNSUPPORTED;
   g.mt = p.mt; g.nt = p.nt; g.splits = p.splits; g.k_per_split = p.kps;
-  const bool vec = vec_ok<E>(g.a, g.lda, AK ? g.K : g.M) &&
-                   vec_ok<E>(g.b, g.ldb, BK ? g.K : g.N) &&
-                   (!g.amask || vec_ok<E>(g.amask, g.lda, AK ? g.K : g.M)) &&
-                   (!g.bmask || vec_ok<E>(g.bmask, g.ldb, BK ? g.K : g.N)) && p.kps % 4 == 0;
+  const bool vec = vec_ok<E>(g.a, g.lda, AK ? g.K : g.M, AK) &&
+                   vec_ok<E>(g.b, g.ldb, BK ? g.K : g.N, BK) &&
+                   (!g.amask || vec_ok<E>(g.amask, g.lda, AK ? g.K : g.M, AK)) &&
+                   (!g.bmask || vec_ok<E>(g.bmask, g.ldb, BK ? g.K : g.N, BK));
   CE* out = (CE*)g.c;
   const int ldo = g.ldc;
   const float* bias = g.bias;
@@ -519,17 +591,16 @@ static sb_status gemm_run(GemmArgs g, float* ws, size_t ws_bytes, hipStream_t st
   if (split) {
     g.c = ws; g.ldc = g.N;
     g.bias = nullptr; g.relu = 0; g.accumulate = 0;
-    g.colsum = nullptr;
+    if (colsum) g.colsum = ws + (size_t)p.splits * g.M * g.N;
+    g.colsum_acc = 0;
   }
   if (vec) gemm_launch<AK, BK, true, E, CE>(p, g, st);
   else gemm_launch<AK, BK, false, E, CE>(p, g, st);
   if (split) {
     const size_t total = (size_t)g.M * g.N;
-    gemm_splitk_epilogue<CE><<<(unsigned)((total + 1023) / 1024), 256, 0, st>>>(
-        ws, p.splits, g.M, g.N, out, ldo, bias, relu, accumulate);
-    if (colsum)
-      col_sum<E><<<cdiv(g.N, 64), 1024, 0, st>>>(csrc, cmask, g.K, g.N, cld, colsum,
-                                                  colsum_acc);
+    const unsigned blocks = (unsigned)((total + 1023) / 1024) + (colsum ? cdiv(g.N, 256) : 0);
+    gemm_splitk_epilogue<CE><<<blocks, 256, 0, st>>>(ws, p.splits, g.M, g.N, out, ldo, bias, relu,
+                                                     accumulate, g.colsum, colsum, colsum_acc);
   }
   return SB_OK;
 }
@@ -600,8 +671,7 @@ extern "C" sb_status sb_fc_shard_fwd(const sb_fc_desc* d, const void* x, const v
 }
 
 // Backward on operands of type E: dx_partial has type E, dW and db fp32.
-// db is added up inside the dW product (or by col_sum when that product is
-// split).
+// db is added up inside the dW product.
 template <class E>
 static sb_status fc_bwd_run(const sb_fc_desc* d, const void* x, const void* w, const void* dy,
                             const void* mask, void* dxp, float* dw, float* db, int accumulate,
@@ -623,8 +693,7 @@ static sb_status fc_bwd_run(const sb_fc_desc* d, const void* x, const void* w, c
   g.M = d->k_in; g.N = d->n_shard; g.K = d->m;
   g.accumulate = accumulate;
   g.colsum = db; g.colsum_acc = accumulate;
-  return gemm_run<false, false, E, float>(g, (float*)ws, ws_bytes, st, (const E*)dy,
-                                          (const E*)mask, d->ldy);
+  return gemm_run<false, false, E, float>(g, (float*)ws, ws_bytes, st);
 }
 
 extern "C" sb_status sb_fc_shard_bwd(const sb_fc_desc* d, const void* x, const void* w,

@@ -50,7 +50,9 @@ constexpr int kSplitA[6] = {2, 1, 1, 0, 0, 0}, kSplitB[6] = {0, 0, 1, 1, 2, 0};
 // A fragment's (or an LDS piece's) eight values as three bf16 pieces.
 struct Split8 { s8 p[3]; };   // high, mid, low
 
-// The triples of two values, packed as bf16 pairs (lo in bits 0..15).
+// The triples of two values, packed as bf16 pairs (lo in bits 0..15).  (The
+// remainders as bf16 pair dot products with (-1, 0) and (0, -1) would be 7
+// instructions instead of 11, but those run slower: FC products 35 -> 38 us.)
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m,
                                            uint32_t& l) {
   h = f32x2_to_bf16x2(a, b);
