@@ -1129,7 +1129,7 @@ sb_status conv_bf16(bool dgrad, int N, int Cin, int H, int W, int Cout, const vo
                     size_t ws_bytes, int relu, bool prepacked, hipStream_t st);
 
 // The split fp32 path (conv_split.hip) for the fp32 shapes it takes.
-bool conv_split_takes(int Cin, int W, int Cout);
+bool conv_split_takes(int N, int Cin, int H, int W, int Cout);
 size_t conv_split_ws(int N, int Cin, int H, int W, int Cout, bool prepacked);
 size_t conv_split_pack_bytes(int N, int Cin, int H, int W, int Cout);
 void conv_split_pack(bool dgrad, int Cin, int Cout, const void* wt, void* packed, hipStream_t st);
@@ -1139,8 +1139,8 @@ sb_status conv_split(bool dgrad, int N, int Cin, int H, int W, int Cout, const v
                      const void* wt, const float* bias, const void* mask, void* out, void* ws,
                      size_t ws_bytes, int relu, bool prepacked, hipStream_t st,
                      uint8_t* pool_idx);
-static bool split_takes(int dtype, int Cin, int W, int Cout) {
-  return dtype == SB_F32 && conv_split_takes(Cin, W, Cout);
+static bool split_takes(int dtype, int N, int Cin, int H, int W, int Cout) {
+  return dtype == SB_F32 && conv_split_takes(N, Cin, H, W, Cout);
 }
 
 // Workspace of a forward / data-gradient call; prepacked: the filters come
@@ -1148,7 +1148,7 @@ static bool split_takes(int dtype, int Cin, int W, int Cout) {
 size_t conv_igemm_ws(int dtype, int N, int Cin, int H, int W, int Cout, bool prepacked) {
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16_ws(N, Cin, H, W, Cout, prepacked);
-  if (split_takes(dtype, Cin, W, Cout)) return conv_split_ws(N, Cin, H, W, Cout, prepacked);
+  if (split_takes(dtype, N, Cin, H, W, Cout)) return conv_split_ws(N, Cin, H, W, Cout, prepacked);
   const int es = (int)dsize(dtype);
   const sb::IgemmPlan p = sb::igemm_plan(N, Cin, H, W, Cout, es, true);
   const sb::IgemmPlan q = sb::igemm_plan(N, Cin, H, W, Cout, es, false);
@@ -1162,7 +1162,7 @@ size_t conv_igemm_ws(int dtype, int N, int Cin, int H, int W, int Cout, bool pre
 size_t conv_igemm_pack_bytes(int dtype, int N, int Cin, int H, int W, int Cout) {
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16_pack_bytes(N, Cin, H, W, Cout);
-  if (split_takes(dtype, Cin, W, Cout)) return conv_split_pack_bytes(N, Cin, H, W, Cout);
+  if (split_takes(dtype, N, Cin, H, W, Cout)) return conv_split_pack_bytes(N, Cin, H, W, Cout);
   return sb::igemm_plan(N, Cin, H, W, Cout, (int)dsize(dtype), false).pack_bytes;
 }
 
@@ -1176,7 +1176,7 @@ int conv_igemm_pack_task(bool dgrad, int dtype, int N, int Cin, int H, int W, in
   t->out = packed;
   t->Cin = Cin;
   t->Cout = Cout;
-  if (split_takes(dtype, Cin, W, Cout)) {
+  if (split_takes(dtype, N, Cin, H, W, Cout)) {
     t->kind = dgrad ? sb::kPackSplitBwd : sb::kPackSplitFwd;
     return sb::cdiv(Cout, 16) * sb::cdiv(Cin, 32);
   }
@@ -1207,7 +1207,7 @@ void conv_igemm_pack(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
     conv_bf16_pack(dgrad, N, Cin, H, W, Cout, wt, packed, st);
     return;
   }
-  if (split_takes(dtype, Cin, W, Cout)) {
+  if (split_takes(dtype, N, Cin, H, W, Cout)) {
     conv_split_pack(dgrad, Cin, Cout, wt, packed, st);
     return;
   }
@@ -1225,7 +1225,7 @@ void conv_igemm_pack(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
 // even image sizes, and a plan that pools for aligned and unaligned tensors.
 bool conv_igemm_pools(int dtype, int N, int Cin, int H, int W, int Cout) {
   if (dtype != SB_F32 || H % 2 || W % 2) return false;
-  if (split_takes(dtype, Cin, W, Cout)) return true;
+  if (split_takes(dtype, N, Cin, H, W, Cout)) return true;
   for (bool aligned : {true, false})
     if (!sb::igemm_pools(sb::igemm_plan(N, Cin, H, W, Cout, 4, aligned), Cout)) return false;
   return true;
@@ -1235,7 +1235,7 @@ int conv_igemm_describe(bool dgrad, int dtype, int N, int Cin, int H, int W, int
                         char* buf, size_t len, bool pool) {
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16_describe(dgrad, N, Cin, H, W, Cout, buf, len);
-  if (split_takes(dtype, Cin, W, Cout))
+  if (split_takes(dtype, N, Cin, H, W, Cout))
     return conv_split_describe(dgrad, N, Cin, H, W, Cout, buf, len, pool);
   sb::IgemmPlan p = sb::igemm_plan(N, Cin, H, W, Cout, (int)dsize(dtype));
   const char* et = dtype == SB_BF16 ? "unsigned short" : "float";
@@ -1261,7 +1261,7 @@ sb_status conv_igemm(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16(dgrad, N, Cin, H, W, Cout, in, wt, bias, mask, out, ws, ws_bytes, relu,
                      prepacked, st);
-  if (split_takes(dtype, Cin, W, Cout))
+  if (split_takes(dtype, N, Cin, H, W, Cout))
     return conv_split(dgrad, N, Cin, H, W, Cout, in, wt, bias, mask, out, ws, ws_bytes, relu,
                       prepacked, st, pool_idx);
   // The whole-image kernels move 4 elements at a time (16 bytes in fp32, 8 in

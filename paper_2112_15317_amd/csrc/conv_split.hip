@@ -405,6 +405,8 @@ using S16C = STile<8, 16, 1, 1, 2, 2>;
 using S8A = STile<8, 8, 1, 4, 1, 1>;
 using S8B = STile<8, 8, 1, 2, 1, 2>;
 using S8C = STile<8, 8, 1, 1, 1, 4>;
+using S4A = STile<4, 4, 4, 4, 1, 1>;
+using S4B = STile<4, 4, 4, 2, 1, 2>;
 struct STileInfo { int th, tw, imgs, wn, wm, wk; const char* name; };
 template <class T> constexpr STileInfo stile_info(const char* name) {
   return {T::TH, T::TW, T::IMGS, T::WN, T::WM, T::WK, name};
@@ -413,6 +415,7 @@ static const STileInfo kSTiles[] = {
     stile_info<S16A>("8, 16, 1, 2, 2, 1"), stile_info<S16B>("16, 16, 1, 1, 4, 1"),
     stile_info<S16C>("8, 16, 1, 1, 2, 2"), stile_info<S8A>("8, 8, 1, 4, 1, 1"),
     stile_info<S8B>("8, 8, 1, 2, 1, 2"),   stile_info<S8C>("8, 8, 1, 1, 1, 4"),
+    stile_info<S4A>("4, 4, 4, 4, 1, 1"),   stile_info<S4B>("4, 4, 4, 2, 1, 2"),
 };
 
 // Tile and split of one pass: the candidate with the least estimated time.
@@ -426,6 +429,7 @@ static SPlan split_plan(int N, int Cin, int H, int W, int Cout) {
   for (int i = 0; i < (int)(sizeof(kSTiles) / sizeof(kSTiles[0])); ++i) {
     const STileInfo& t = kSTiles[i];
     if (t.tw > 8 && W <= 8) continue;
+    if (t.tw == 4 && W >= 8) continue;
     SPlan p{};
     p.tile = i;
     p.imgs = t.imgs;
@@ -489,7 +493,9 @@ static void split_dispatch(const SPlan& p, const ConvArgs& a, hipStream_t st) {
     case 2: split_launch<S16C, DGRAD>(p, a, st); break;
     case 3: split_launch<S8A, DGRAD>(p, a, st); break;
     case 4: split_launch<S8B, DGRAD>(p, a, st); break;
-    default: split_launch<S8C, DGRAD>(p, a, st); break;
+    case 5: split_launch<S8C, DGRAD>(p, a, st); break;
+    case 6: split_launch<S4A, DGRAD>(p, a, st); break;
+    default: split_launch<S4B, DGRAD>(p, a, st); break;
   }
 }
 
@@ -497,12 +503,21 @@ static void split_dispatch(const SPlan& p, const ConvArgs& a, hipStream_t st) {
 
 namespace sbh {
 
-// Whether an fp32 pass runs here: images at least 8 wide (narrower whole
-// images have kernels that skip the padded taps), more than 16 input channels
-// (a chunk is 32) and, on wide images, more than 16 output channels (a tile is
-// 64); the fp32-MFMA kernels of conv_igemm.hip take the others.
-bool conv_split_takes(int Cin, int W, int Cout) {
-  return W >= 8 && Cin > 16 && !(W >= 32 && Cout <= 16);
+// Whether an fp32 pass runs here; the fp32-MFMA kernels of conv_igemm.hip take
+// the others.  Never: images narrower than 4 (2x2 kernels skip the 56 % of the
+// products that are padding), 16 input channels or fewer (a chunk is 32), wide
+// images of 16 output channels or fewer (a tile is 64).  Otherwise by work, as
+// a block needs about 12 us for a tile of one chunk and the chip 256 of them:
+// with v = pixels x Cin x Cout, from 4e7 on, or from 1.2e7 on where at least
+// 6144 pixels make enough tiles.  Forward and data gradient in us, on the fp32
+// MFMA and here: 16x16 128 -> 128, 8 images (3.4e7, 2048 pixels) 44, 50; 16x16
+// 64 -> 48, 20 images (1.6e7, 5120 pixels) 38, 42; 4x4 512 -> 512, 16 images
+// (6.7e7) 85, 64; 14x14 50 -> 60, 40 images (2.4e7, 7840 pixels) 58, 48; 10x10
+// 20 -> 64, 100 images (1.3e7, 10000 pixels) 65, 45.
+bool conv_split_takes(int N, int Cin, int H, int W, int Cout) {
+  if (W < 4 || Cin <= 16 || (W >= 32 && Cout <= 16)) return false;
+  const double px = (double)N * H * W, v = px * Cin * Cout;
+  return v >= 4e7 || (W >= 8 && px >= 6144 && v >= 1.2e7);
 }
 
 size_t conv_split_ws(int N, int Cin, int H, int W, int Cout, bool prepacked) {
