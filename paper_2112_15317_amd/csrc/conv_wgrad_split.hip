@@ -14,6 +14,12 @@
 // the pixels, a fourth of what four waves with output blocks of their own
 // would (all accumulators of the chip are 38 MB).
 //
+// Rounding.  The MFMA drops low bits always in one direction, so the local
+// sums of 32 pixels are off by a little with the same sign and over 1e5 pixels
+// that adds up (dw of 128 images of 32x32 against 64 bits: 4.4e-7, on the fp32
+// MFMA 4.0e-7).  dy is therefore negated for the odd waves' pixels as it is
+// staged, and their sums are subtracted: the shares cancel (1.2e-7).
+//
 //   * Staging: a lane loads 8 channels of 4 consecutive pixels as fp32 NCHW
 //     (16-byte loads where rows are whole aligned quads), splits them, and
 //     stores each pixel as three 16-byte pieces [part][channel / 8][pixel]
@@ -113,16 +119,13 @@ __device__ __forceinline__ float wgrad_one(const WsArgs& a, int k, int c, int ta
 
 // VEC: rows are whole aligned quads (W a multiple of 4, 16-byte tensors), so a
 // quad of one channel is one 16-byte load.
+// The work of block b of the layer `a`; the kernels below pick both.
 template <class T, bool VEC>
-__global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
+__device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
   extern __shared__ u16 ldsu[];
   float* E = reinterpret_cast<float*>(ldsu);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Blocks in (split, k tile, c tile) order, dealt to the 8 XCDs in contiguous
-  // ranges: the blocks of a split read the same pixel tiles through one L2.
-  int b = blockIdx.x;
-  if (gridDim.x % 8 == 0) b = (b % 8) * (gridDim.x / 8) + b / 8;
   const int k_tiles = cdiv(a.K, T::BK);
   const int ct = b % a.c_tiles, kt = b / a.c_tiles % k_tiles, split = b / (a.c_tiles * k_tiles);
   const int c0 = ct * T::BC, k0 = kt * T::BK;
@@ -140,6 +143,7 @@ __global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
     const int dimg = dp / (T::TH * T::TW), dyy = dp / T::TW % T::TH, dxx = dp % T::TW;
     const int d_rel = (dimg * a.K + k0 + doct * 8) * HWs + dyy * a.W + dxx;
     const int d_lds = (doct * T::DPL + dp) * 8;
+    const uint32_t dneg = dp & 32 ? 0x80000000u : 0u;      // odd waves' pixels: negated
     // x quad: lanes from 0 up; x edge pixel: lanes from 255 down.
     const int qrow = ptid % (T::IMGS * T::HH * (T::TW / 4)) / (T::TW / 4);
     const int qoct = ptid / (T::IMGS * T::HH * (T::TW / 4));
@@ -197,6 +201,7 @@ __global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
                        xr, (int)(eok && j < ech ? (uint32_t)(e_rel + base) * 4u : kOOB),
                        j * HWs * 4, 0));
     };
+    auto neg = [&](float v) { return __uint_as_float(__float_as_uint(v) ^ dneg); };
     auto put = [&](u16* at, int part, f8v v) {
       const Split8 s = split8(v);
 #pragma unroll
@@ -211,8 +216,9 @@ __global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        put(B + d_lds + e * 8, T::DPART, f8v{rd[0][e], rd[1][e], rd[2][e], rd[3][e],
-                                             rd[4][e], rd[5][e], rd[6][e], rd[7][e]});
+        put(B + d_lds + e * 8, T::DPART, f8v{neg(rd[0][e]), neg(rd[1][e]), neg(rd[2][e]),
+                                             neg(rd[3][e]), neg(rd[4][e]), neg(rd[5][e]),
+                                             neg(rd[6][e]), neg(rd[7][e])});
       if (q_on) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -322,7 +328,11 @@ __global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
     if (k >= a.K || col >= cw) continue;
     f4 v = *reinterpret_cast<const f4*>(E + row * T::RP + col);
 #pragma unroll
-    for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f4*>(E + w * T::COPY + row * T::RP + col);
+    for (int w = 1; w < 4; ++w) {
+      const f4 u = *reinterpret_cast<const f4*>(E + w * T::COPY + row * T::RP + col);
+      if (w & 1) v -= u;
+      else v += u;
+    }
     if (__builtin_expect(split_suspect(v[0]) || split_suspect(v[1]) || split_suspect(v[2]) ||
                              split_suspect(v[3]), 0)) {
 #pragma unroll
@@ -341,6 +351,38 @@ __global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
   }
   if (do_db && tid < T::BK && k0 + tid < a.K)
     (a.splits == 1 ? a.db : dst + wsz)[k0 + tid] = E[4 * T::COPY + tid];
+}
+
+// Blocks in (split, k tile, c tile) order, dealt to the 8 XCDs in contiguous
+// ranges: the blocks of a split read the same pixel tiles through one L2.
+__device__ __forceinline__ int ws_deal(int b, int nb) {
+  return nb % 8 == 0 ? (b % 8) * (nb / 8) + b / 8 : b;
+}
+
+template <class T, bool VEC>
+__global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split(WsArgs a) {
+  wgrad_split_block<T, VEC>(a, ws_deal(blockIdx.x, gridDim.x));
+}
+
+// Weight gradients of up to kWsMany layers that take the same kernel, in one
+// launch: layer i owns the blocks first[i] .. first[i+1]-1 and numbers them as
+// its own grid would be.  A layer's grid is about one block per CU, so the
+// next layer's blocks start on the CUs that finish first instead of after the
+// last block and a launch.
+constexpr int kWsMany = 4;
+struct WsMany {
+  WsArgs a[kWsMany];
+  int first[kWsMany + 1];
+  int n;
+};
+
+template <class T, bool VEC>
+__global__ __launch_bounds__(512, 2) void conv3x3_wgrad_split_many(WsMany m) {
+  const int blk = blockIdx.x;
+  int i = 0;
+  while (i + 1 < m.n && blk >= m.first[i + 1]) ++i;
+  const int nb = m.first[i + 1] - m.first[i], b = blk - m.first[i];
+  wgrad_split_block<T, VEC>(m.a[i], m.first[i] % 8 == 0 ? ws_deal(b, nb) : b);
 }
 
 // ---------------------------------------------------------------- host --
@@ -367,6 +409,8 @@ static WsPlan ws_plan(int N, int C, int H, int W, int K) {
   for (int i = 0; i < 3; ++i) {
     const WsTileInfo& t = kWsTiles[i];
     const long n = (long)cdiv(W, t.tw) * cdiv(H, t.th) * cdiv(N, t.imgs);
+    // A tile's images have to stay below 2^31 bytes.
+    if (i > 0 && (int64_t)std::min(t.imgs, N) * std::max(C, K) * H * W * 4 >= (1ll << 31)) continue;
     if (i == 0 || n < least) {
       least = n;
       p.tile = i;
@@ -409,10 +453,34 @@ static void ws_launch(const WsPlan& p, const WsArgs& a, hipStream_t st) {
   conv3x3_wgrad_split<T, VEC>
       <<<(unsigned)(p.k_tiles * p.c_tiles * p.splits), 512, T::LDS_BYTES, st>>>(a);
 }
+static bool ws_vec(int W, const void* x, const void* dy) {
+  return W % 4 == 0 && (((uintptr_t)x | (uintptr_t)dy) & 15) == 0;
+}
 template <class T>
 static void ws_launch(const WsPlan& p, const WsArgs& a, hipStream_t st) {
-  if (a.W % 4 == 0 && (((uintptr_t)a.x | (uintptr_t)a.dy) & 15) == 0) ws_launch<T, true>(p, a, st);
+  if (ws_vec(a.W, a.x, a.dy)) ws_launch<T, true>(p, a, st);
   else ws_launch<T, false>(p, a, st);
+}
+
+template <class T, bool VEC>
+static void ws_launch_many(const WsMany& m, hipStream_t st) {
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute((const void*)conv3x3_wgrad_split_many<T, VEC>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
+  });
+  conv3x3_wgrad_split_many<T, VEC><<<(unsigned)m.first[m.n], 512, T::LDS_BYTES, st>>>(m);
+}
+
+static WsArgs ws_args(const WsPlan& p, int N, int C, int H, int W, int K, const void* x,
+                      const void* dy, float* dw, float* db, void* ws) {
+  WsArgs a{};
+  a.x = (const float*)x; a.dy = (const float*)dy; a.dw = dw; a.db = db;
+  a.part = p.splits > 1 ? (float*)ws : nullptr;
+  a.N = N; a.C = C; a.H = H; a.W = W; a.K = K;
+  a.tiles_w = p.tiles_w; a.tiles_h = p.tiles_h; a.ptiles = p.ptiles;
+  a.tiles_per_split = p.tps; a.c_tiles = p.c_tiles; a.splits = p.splits;
+  return a;
 }
 
 }  // namespace sb
@@ -423,10 +491,16 @@ void conv_wgrad_reduce(const float* part, int splits, int K, int C, float* dw, f
                        hipStream_t st);
 
 // Whether an fp32 weight gradient runs here: at least 8 input channels (the
-// narrow kernels flatten fewer), and images other than 2x2, whose gradient is a
-// dense product without padding (conv3x3_wgrad_2x2).
-bool conv_wgrad_split_takes(int C, int H, int W) {
-  return C >= 8 && W >= 4 && !(H == 2 && W == 2);
+// narrow kernels flatten fewer), images at least 4 wide, and enough work for
+// 128-pixel tiles where they suit the image less.  With v = pixels x C x K:
+// narrower than 8, from 1.4e7 on (100 images of 4x6, 64 channels, 9.8e6: 15 us
+// on the fp32 MFMA, 20 here; 64 of 5x7, 100 -> 75, 1.7e7: 26, 20); rows that
+// are not whole quads (4-byte loads), from 7e6 on (8 images of 24x17, 32 -> 40,
+// 4.2e6: 14.4, 16.2; 30 of 9x11, 16 -> 200, 9.5e6: 22, 19); any other.
+bool conv_wgrad_split_takes(int N, int C, int H, int W, int K) {
+  if (C < 8 || W < 4) return false;
+  const double v = (double)N * H * W * C * K;
+  return W < 8 ? v >= 1.4e7 : W % 4 == 0 || v >= 7e6;
 }
 
 size_t conv_wgrad_split_ws(int N, int C, int H, int W, int K) {
@@ -446,18 +520,63 @@ sb_status conv_wgrad_split(int N, int C, int H, int W, int K, const void* x, con
   if ((int64_t)std::min(p.imgs, N) * std::max(C, K) * H * W * 4 >= (1ll << 31))
     return SB_ERR_UNSUPPORTED;
   if (p.ws_bytes > 0 && (ws == nullptr || ws_bytes < p.ws_bytes)) return SB_ERR_WORKSPACE;
-  sb::WsArgs a{};
-  a.x = (const float*)x; a.dy = (const float*)dy; a.dw = dw; a.db = db;
-  a.part = p.splits > 1 ? (float*)ws : nullptr;
-  a.N = N; a.C = C; a.H = H; a.W = W; a.K = K;
-  a.tiles_w = p.tiles_w; a.tiles_h = p.tiles_h; a.ptiles = p.ptiles;
-  a.tiles_per_split = p.tps; a.c_tiles = p.c_tiles; a.splits = p.splits;
+  const sb::WsArgs a = sb::ws_args(p, N, C, H, W, K, x, dy, dw, db, ws);
   switch (p.tile) {
     case 0: sb::ws_launch<sb::Ws16>(p, a, st); break;
     case 1: sb::ws_launch<sb::Ws8>(p, a, st); break;
     default: sb::ws_launch<sb::Ws4>(p, a, st); break;
   }
   if (p.splits > 1) conv_wgrad_reduce(a.part, p.splits, K, C, dw, db, st);
+  return launch_status();
+}
+
+// Batch key of an NCHW weight gradient: layers on the same instantiation of
+// the kernel above share a key; -1 for a layer that takes another kernel or
+// that the kernel refuses (it runs on its own).
+int conv_wgrad_batch_key(int dtype, int N, int C, int H, int W, int K, const void* x,
+                         const void* dy) {
+  if (dtype != SB_F32 || !conv_wgrad_split_takes(N, C, H, W, K)) return -1;
+  const sb::WsPlan p = sb::ws_plan(N, C, H, W, K);
+  if ((int64_t)std::min(p.imgs, N) * std::max(C, K) * H * W * 4 >= (1ll << 31)) return -1;
+  return p.tile * 2 + (sb::ws_vec(W, x, dy) ? 1 : 0);
+}
+
+// n (1..4) layers with one batch key on one launch: the same partials,
+// reductions and results as n single calls.  shape[i] = {N, C, H, W, K};
+// ws[i] / ws_bytes[i]: layer i's own workspace region.
+sb_status conv_wgrad_group(int n, const int (*shape)[5], const void* const* x,
+                           const void* const* dy, float* const* dw, float* const* db,
+                           void* const* ws, const size_t* ws_bytes, hipStream_t st) {
+  if (n < 1 || n > sb::kWsMany) return SB_ERR_INVALID_ARG;
+  sb::WsPlan p[sb::kWsMany];
+  sb::WsMany m{};
+  m.n = n;
+  int key = -1, total = 0;
+  for (int i = 0; i < n; ++i) {
+    const int N = shape[i][0], C = shape[i][1], H = shape[i][2], W = shape[i][3],
+              K = shape[i][4];
+    const int k = conv_wgrad_batch_key(SB_F32, N, C, H, W, K, x[i], dy[i]);
+    if (k < 0 || (i > 0 && k != key)) return SB_ERR_INVALID_ARG;
+    key = k;
+    p[i] = sb::ws_plan(N, C, H, W, K);
+    if (p[i].ws_bytes > 0 && (ws[i] == nullptr || ws_bytes[i] < p[i].ws_bytes))
+      return SB_ERR_WORKSPACE;
+    m.a[i] = sb::ws_args(p[i], N, C, H, W, K, x[i], dy[i], dw[i], db ? db[i] : nullptr, ws[i]);
+    m.first[i] = total;
+    total += p[i].k_tiles * p[i].c_tiles * p[i].splits;
+  }
+  for (int i = n; i <= sb::kWsMany; ++i) m.first[i] = total;
+  switch (key) {
+    case 0: sb::ws_launch_many<sb::Ws16, false>(m, st); break;
+    case 1: sb::ws_launch_many<sb::Ws16, true>(m, st); break;
+    case 2: sb::ws_launch_many<sb::Ws8, false>(m, st); break;
+    case 3: sb::ws_launch_many<sb::Ws8, true>(m, st); break;
+    case 4: sb::ws_launch_many<sb::Ws4, false>(m, st); break;
+    default: sb::ws_launch_many<sb::Ws4, true>(m, st); break;
+  }
+  for (int i = 0; i < n; ++i)
+    if (p[i].splits > 1)
+      conv_wgrad_reduce(m.a[i].part, p[i].splits, m.a[i].K, m.a[i].C, m.a[i].dw, m.a[i].db, st);
   return launch_status();
 }
 

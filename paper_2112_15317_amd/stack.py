@@ -223,12 +223,12 @@ class ConvStack:
     @staticmethod
     def group_wgrads(descs, most=4):
         """Groups (of two or more, at most `most`) of consecutive layers, in
-        backward order, whose weight gradients run on the same fp32 wide-tile
+        backward order, whose weight gradients run on the same fp32
         kernel, which sb_conv3x3_bwd_weight_many then issues as one launch:
         host-side queries only."""
         def name(d):
             s = sb.sb_conv3x3_plan_string(d, sb.SB_PASS_BWD_WEIGHT).split(" grid=")[0]
-            return s if re.fullmatch(r"sb::conv3x3_wgrad_f32<sb::WgTile<\d+, \d+, \d+, 0>, float>",
+            return s if re.fullmatch(r"sb::conv3x3_wgrad_split<sb::WsTile<\d+, \d+, \d+>, \w+>",
                                      s) else None
         groups, run = [], []
         for i in reversed(range(len(descs))):
