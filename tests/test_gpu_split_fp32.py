@@ -1,0 +1,217 @@
+"""The fp32 kernels that multiply on the bf16 MFMA (operands split in three bf16
+parts) against 64-bit sums: every tile of the convolution passes split and
+unsplit, at ragged sizes, aligned and not; sums over many pixels, whose rounding
+must not drift; infinities, NaNs and tiny values; the FC products; and the
+rules that choose these kernels, host-side."""
+import pytest
+import torch
+
+from paper_2112_15317_amd import sb
+from tests.helpers import print_case, rel_l2
+
+# The products are exact to half an fp32 rounding and a sum is rounded to fp32
+# once per 32 terms.  The shapes here sum up to 113 such blocks in a row (397
+# channels x 9 taps): sqrt(113 / 2) * 2^-24 = 4.5e-7 for a random walk of
+# roundings against a random walk of terms.
+REL = 5e-7
+
+# (n, c, h, w, k): between them every tile of the forward and of the data
+# gradient, with and without split partials, and the three tiles of the weight
+# gradient with whole and with broken pixel quads.
+SHAPES = [(27, 95, 9, 33, 26), (43, 29, 9, 40, 27), (27, 24, 9, 33, 90), (22, 375, 9, 7, 77),
+          (41, 40, 9, 4, 678), (100, 261, 8, 4, 48), (45, 91, 9, 7, 162), (30, 171, 9, 6, 145),
+          (303, 23, 8, 4, 180), (154, 131, 9, 6, 37), (286, 151, 4, 9, 17), (49, 41, 5, 40, 30),
+          (76, 18, 8, 16, 129), (149, 20, 4, 16, 64), (65, 82, 8, 9, 106), (19, 18, 16, 33, 67),
+          (17, 246, 9, 16, 67), (59, 139, 16, 8, 16), (36, 70, 30, 8, 20), (50, 19, 16, 8, 157),
+          (4, 151, 9, 20, 369), (29, 36, 30, 8, 48), (51, 99, 5, 5, 317), (40, 65, 9, 8, 217),
+          (72, 22, 30, 8, 32), (39, 397, 8, 5, 66), (40, 50, 14, 14, 60)]
+PASSES = (sb.SB_PASS_FWD, sb.SB_PASS_BWD_DATA, sb.SB_PASS_BWD_WEIGHT)
+
+
+def _plan(shape, p):
+    n, c, h, w, k = shape
+    return sb.sb_conv3x3_plan_string(sb.conv_desc(n, c, h, w, k, sb.SB_F32), p)
+
+
+def test_shapes_reach_every_tile():
+    for p in PASSES[:2]:
+        seen = {(s.split("STile<")[1].split(">")[0], s.endswith("x1"))
+                for s in (_plan(q, p) for q in SHAPES) if "conv3x3_split_f32" in s}
+        assert len(seen) == 16, seen                        # 8 tiles, split or not
+    seen = {s.split(" grid")[0] for s in (_plan(q, PASSES[2]) for q in SHAPES)}
+    assert len([s for s in seen if "conv3x3_wgrad_split" in s]) == 6, seen
+
+
+@pytest.mark.parametrize("shape,passes", [
+    ((8, 128, 16, 16, 128), "--w"),      # 2048 pixels, 3.4e7 products: below 4e7
+    ((24, 64, 16, 16, 64), "fdw"),       # 6144 pixels, 2.5e7
+    ((24, 64, 16, 15, 64), "--w"),       # 5760 pixels
+    ((64, 24, 32, 32, 16), "--w"),       # 16 outputs; the data gradient has 16 inputs
+    ((64, 16, 32, 32, 64), "--w"), # a chunk is 32 channels; the gradient has 16 outputs
+    ((16, 512, 4, 4, 512), "fdw"),
+    ((8, 512, 4, 4, 512), "--w"),        # 3.4e7 on narrow images
+    ((128, 512, 2, 2, 512), "---"),
+    ((8, 32, 24, 17, 40), "---"),        # rows of broken quads, below 7e6
+    ((8, 32, 24, 16, 40), "--w"),
+    ((100, 64, 4, 6, 64), "---"),        # narrow images, below 1.4e7
+    ((128, 3, 32, 32, 64), "---"),
+])
+def test_rule(shape, passes):
+    for p, want in zip(PASSES, passes):
+        assert ("split" in _plan(shape, p)) == (want != "-"), _plan(shape, p)
+
+
+def test_large_images_take_a_tile_within_range():
+    # 8 images of this size pass 2^31 bytes, 2 do not.  The size's least padded
+    # tiles would be 4 x 4 x 8 images.
+    assert "WsTile<8, 8, 2>" in _plan((8, 64, 1364, 1364, 64), sb.SB_PASS_BWD_WEIGHT)
+
+
+def _rand(*shape, seed=0, scale=1.0):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randn(*shape, generator=g) * scale
+
+
+def _dev(t, off=0):
+    """On the GPU, starting `off` floats past a 16-byte boundary."""
+    buf = torch.empty(t.numel() + off, device="cuda")
+    buf[off:].copy_(t.reshape(-1))
+    return buf[off:].view(t.shape)
+
+
+def _ws(nbytes):
+    return torch.full((max(int(nbytes), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+
+
+def _run(shape, x, w, b, dy, off=0, mask=None):
+    n, c, h, wd, k = shape
+    d = sb.conv_desc(n, c, h, wd, k, sb.SB_F32)
+    ws = _ws(max(sb.sb_conv3x3_workspace_bytes(d, p) for p in PASSES))
+    xd, wt, bd, dyd = _dev(x, off), _dev(w), _dev(b), _dev(dy, off)
+    y, dx = _dev(torch.full_like(dy, 7.0), off), _dev(torch.full_like(x, 7.0), off)
+    dw, db = torch.full((k, c, 3, 3), 7.0, device="cuda"), torch.full((k,), 7.0, device="cuda")
+    sb.sb_conv3x3_fwd(d, xd, wt, bd, y, ws)
+    sb.sb_conv3x3_bwd_data(d, dyd, wt, _dev(mask, off) if mask is not None else None, dx, ws)
+    sb.sb_conv3x3_bwd_weight(d, xd, dyd, dw, db, ws)
+    torch.cuda.synchronize()
+    return [t.cpu() for t in (y, dx, dw, db)]
+
+
+def _ref(x, w, b, dy, dt=torch.float64):
+    x, w, b, dy = (t.to(dt) for t in (x, w, b, dy))
+    return [torch.nn.functional.conv2d(x, w, b, padding=1),
+            torch.nn.grad.conv2d_input(x.shape, w, dy, padding=1),
+            torch.nn.grad.conv2d_weight(x, w.shape, dy, padding=1), dy.sum((0, 2, 3))]
+
+
+def _inputs(shape, xs=1.0, ws=1.0):
+    n, c, h, w, k = shape
+    return (_rand(n, c, h, w, seed=1, scale=xs), _rand(k, c, 3, 3, seed=2, scale=ws / (3 * c ** 0.5)),
+            _rand(k, seed=3, scale=0.1 * xs * ws), _rand(n, k, h, w, seed=4, scale=xs))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_conv_against_64_bits(shape, off):
+    print_case("split conv", shape=shape, off=off)
+    x, w, b, dy = _inputs(shape)
+    mask = _rand(*x.shape, seed=5)
+    got, ref = _run(shape, x, w, b, dy, off, mask), _ref(x, w, b, dy)
+    ref[1] = ref[1] * (mask > 0)
+    for name, a, r in zip(("y", "dx", "dw", "db"), got, ref):
+        assert rel_l2(a, r) < REL, (name, rel_l2(a, r))
+
+
+@pytest.mark.gpu
+def test_weight_gradient_does_not_drift():
+    # 131072 pixels of positive x against zero-mean dy.  Local sums that are all
+    # rounded in one direction leave 4.4e-7; without a drift the blocks of 32
+    # pixels, the waves and the splits add about 20 roundings in a row:
+    # sqrt(20 / 2) * 2^-24 = 1.9e-7.
+    shape = (128, 32, 32, 32, 24)
+    print_case("wgrad drift", shape=shape)
+    x, w, b, dy = _inputs(shape)
+    x = torch.relu(x)
+    dw, ref = _run(shape, x, w, b, dy)[2], _ref(x, w, b, dy)[2]
+    assert rel_l2(dw, ref) < 2.2e-7, rel_l2(dw, ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(24, 64, 16, 16, 64), (40, 80, 4, 4, 800), (36, 72, 30, 8, 20)])
+def test_conv_values_the_split_cannot_carry(shape):
+    print_case("split conv special", shape=shape)
+    # Products of 2^-110: low parts below the bf16 range.  Plain fp32 sums then:
+    # up to 7200 roundings in a row.
+    x, w, b, dy = _inputs(shape, xs=2.0 ** -60, ws=2.0 ** -50)
+    got, ref = _run(shape, x, w, torch.zeros_like(b), dy), _ref(x, w, torch.zeros_like(b), dy)
+    for a, r in zip(got[:2], ref[:2]):
+        assert rel_l2(a, r) < (7200 / 2) ** 0.5 * 2.0 ** -24, rel_l2(a, r)
+    # One infinity, one NaN and one value that would round to infinity.
+    x, w, b, dy = _inputs(shape)
+    x[1, 3, 1, 2], x[2, 5, 3, 0], x[3, 4, 0, 3] = float("inf"), float("nan"), 3.4e38
+    dy[4, 6, 2, 1] = float("-inf")
+    got, ref = _run(shape, x, w, b, dy), _ref(x, w, b, dy, torch.float32)
+    for name, a, r in zip(("y", "dx", "dw", "db"), got, ref):
+        same = (torch.isnan(a) == torch.isnan(r)) & (torch.isinf(a) == torch.isinf(r))
+        # 3.4e38 times a filter or a sum with it may round past the range in one order only.
+        assert same.float().mean() > 0.999, name
+        ok = torch.isfinite(a) & torch.isfinite(r) & (r.abs() < 1e30)
+        assert rel_l2(a[ok], r[ok]) < 1e-5, name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(24, 64, 16, 16, 64), (33, 256, 4, 4, 300), (18, 68, 30, 8, 136),
+                                   (28, 69, 4, 40, 78)])
+def test_pooled_forward_is_the_forward_pooled(shape):
+    print_case("split conv pool", shape=shape)
+    n, c, h, wd, k = shape
+    x, w, b, _ = _inputs(shape)
+    d = sb.conv_desc(n, c, h, wd, k, sb.SB_F32)
+    need = max(sb.sb_conv3x3_workspace_bytes(d, p) for p in (sb.SB_PASS_FWD, sb.SB_PASS_FWD_POOL))
+    xd, wt, bd, ws = _dev(x), _dev(w), _dev(b), _ws(need)
+    z = torch.empty(n, k, h, wd, device="cuda")
+    sb.sb_conv3x3_fwd(d, xd, wt, bd, z, ws)
+    out = []
+    for fused in (False, True):
+        y = torch.full((n, k, h // 2, wd // 2), 7.0, device="cuda")
+        idx = torch.full(y.shape, 99, dtype=torch.uint8, device="cuda")
+        if fused:
+            sb.sb_conv3x3_fwd_pool(d, xd, wt, bd, y, idx, ws)
+        else:
+            sb.sb_relu_maxpool_fwd(n, k, h, wd, sb.SB_F32, sb.SB_NCHW, z, y, idx)
+        out.append((y, idx))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,ki,ns", [(1, 33, 1), (63, 65, 127), (64, 64, 64), (65, 31, 130),
+                                     (128, 256, 128), (129, 1000, 66), (512, 512, 1024),
+                                     (1000, 130, 40), (32, 4100, 257)])
+def test_fc_against_64_bits(m, ki, ns):
+    print_case("split fc", m=m, ki=ki, ns=ns)
+    x, w, b = _rand(m, ki, seed=1), _rand(ki, ns, seed=2, scale=ki ** -0.5), _rand(ns, seed=3)
+    dy, mask = _rand(m, ns, seed=4), _rand(m, ns, seed=5)
+    g = dy.double() * (mask > 0)
+    ref = [x.double() @ w.double() + b.double(), g @ w.double().T, x.double().T @ g, g.sum(0)]
+
+    def run(x, dy):
+        d = sb.fc_desc(m, ki, ns, sb.SB_F32)
+        ws = _ws(max(sb.sb_fc_workspace_bytes(d, p) for p in (sb.SB_FC_FWD, sb.SB_FC_BWD)))
+        xd, wt, dyd = _dev(x), _dev(w), _dev(dy)
+        y, dx = torch.full((m, ns), 7.0, device="cuda"), torch.full((m, ki), 7.0, device="cuda")
+        dw, db = torch.full((ki, ns), 7.0, device="cuda"), torch.full((ns,), 7.0, device="cuda")
+        sb.sb_fc_shard_fwd(d, xd, wt, _dev(b), y, ws)
+        sb.sb_fc_shard_bwd(d, xd, wt, dyd, _dev(mask), dx, dw, db, False, ws)
+        torch.cuda.synchronize()
+        return [t.cpu() for t in (y, dx, dw, db)]
+
+    for name, a, r in zip(("y", "dx", "dw", "db"), run(x, dy), ref):
+        assert rel_l2(a, r) < REL, (name, rel_l2(a, r))
+    # An infinity in x reaches its row of y and of dw alone.
+    x[m // 2, ki // 2] = float("inf")
+    y, _, dw, _ = run(x, dy)
+    assert torch.isinf(y).any(1).nonzero().flatten().tolist() == [m // 2]
+    bad = ~torch.isfinite(dw).all(1)
+    assert bad.nonzero().flatten().tolist() == [ki // 2] and not torch.isfinite(dw[ki // 2]).any()
