@@ -14,8 +14,9 @@
 //
 // sgd_update_kernel: a batch of tensors in one launch (as the filter packing
 // does): blocks of tensor t are block0[t] .. block0[t+1]-1, each thread
-// updates 4 consecutive elements with 16-byte loads and stores when the
-// tensor allows it.  Pure HBM stream: 12 bytes per element.
+// updates four groups of 4 consecutive elements, all loads in flight before
+// the first store, with 16-byte moves when the tensor allows it; the block's
+// tensor is found by bisection.  Pure HBM stream: 12 bytes per element.
 #include "sb_internal.hpp"
 
 #include <cmath>
@@ -76,24 +77,49 @@ struct SgdBatch {
   int count;
 };
 
+constexpr int kSgdBlock = 4096;              // elements per block
+
 __global__ __launch_bounds__(256) void sgd_update_kernel(SgdBatch b) {
   const int blk = blockIdx.x;
-  int t = 0;
-  while (t + 1 < b.count && b.block0[t + 1] <= blk) ++t;
-  const size_t i = ((size_t)(blk - b.block0[t]) * 256 + threadIdx.x) * 4;
+  int t = 0, hi = b.count;                   // the last tensor whose blocks start by blk
+  while (hi - t > 1) {
+    const int mid = (t + hi) / 2;
+    if (b.block0[mid] <= blk) t = mid;
+    else hi = mid;
+  }
+  const size_t i0 = (size_t)(blk - b.block0[t]) * kSgdBlock + threadIdx.x * 4;
   const size_t n = b.n[t];
-  if (i >= n) return;
   float* w = b.w[t];
   const float* g = b.g[t];
   const float a = -b.step[t];
-  if (b.vec[t] && i + 4 <= n) {
-    f4 wv = *reinterpret_cast<const f4*>(w + i);
-    const f4 gv = *reinterpret_cast<const f4*>(g + i);
+  constexpr int U = kSgdBlock / 1024;
+  if (b.vec[t] && i0 + (U - 1) * 1024 + 4 <= n) {
+    f4 wv[U], gv[U];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) wv[j] = fmaf(a, gv[j], wv[j]);
-    *reinterpret_cast<f4*>(w + i) = wv;
-  } else {
-    for (size_t j = i; j < i + 4 && j < n; ++j) w[j] = fmaf(a, g[j], w[j]);
+    for (int u = 0; u < U; ++u) {
+      wv[u] = *reinterpret_cast<const f4*>(w + i0 + u * 1024);
+      gv[u] = *reinterpret_cast<const f4*>(g + i0 + u * 1024);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) wv[u][j] = fmaf(a, gv[u][j], wv[u][j]);
+      *reinterpret_cast<f4*>(w + i0 + u * 1024) = wv[u];
+    }
+    return;
+  }
+  for (int u = 0; u < U; ++u) {
+    const size_t i = i0 + (size_t)u * 1024;
+    if (i >= n) return;
+    if (b.vec[t] && i + 4 <= n) {
+      f4 wv = *reinterpret_cast<const f4*>(w + i);
+      const f4 gv = *reinterpret_cast<const f4*>(g + i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) wv[j] = fmaf(a, gv[j], wv[j]);
+      *reinterpret_cast<f4*>(w + i) = wv;
+    } else {
+      for (size_t j = i; j < i + 4 && j < n; ++j) w[j] = fmaf(a, g[j], w[j]);
+    }
   }
 }
 
@@ -149,7 +175,7 @@ extern "C" sb_status sb_sgd_update(int count, float* const* w, const float* cons
       if (u < t && sbh::overlaps(w[t], bytes, w[u], ub)) return SB_ERR_INVALID_ARG;
     }
     b.vec[t] = (((uintptr_t)w[t] | (uintptr_t)g[t]) & 15) == 0;
-    blocks += (long)((n[t] + 1023) / 1024);
+    blocks += (long)((n[t] + sb::kSgdBlock - 1) / sb::kSgdBlock);
     if (blocks >= (1l << 31)) return SB_ERR_UNSUPPORTED;
   }
   b.block0[count] = (int)blocks;
