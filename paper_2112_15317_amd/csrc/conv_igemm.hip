@@ -1261,9 +1261,6 @@ sb_status conv_igemm(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
   if (dtype == SB_BF16 && conv_bf16_takes(N, Cin, H, W, Cout))
     return conv_bf16(dgrad, N, Cin, H, W, Cout, in, wt, bias, mask, out, ws, ws_bytes, relu,
                      prepacked, st);
-  if (split_takes(dtype, N, Cin, H, W, Cout))
-    return conv_split(dgrad, N, Cin, H, W, Cout, in, wt, bias, mask, out, ws, ws_bytes, relu,
-                      prepacked, st, pool_idx);
   // The whole-image kernels move 4 elements at a time (16 bytes in fp32, 8 in
   // bf16); the plan only picks them for tensors aligned that far.
   const uintptr_t amask = dtype == SB_BF16 ? 7 : 15;
@@ -1271,10 +1268,13 @@ sb_status conv_igemm(bool dgrad, int dtype, int N, int Cin, int H, int W, int Co
   const int64_t es = dsize(dtype);
   sb::IgemmPlan p = sb::igemm_plan(N, Cin, H, W, Cout, (int)es, aligned);
   // Buffer ranges: one block's images of the input, and one output-channel
-  // tile's packed filters.
+  // tile's packed filters.  The same sizes are refused whichever kernel runs.
   if ((int64_t)std::min(p.imgs, N) * Cin * H * W * es >= (1ll << 31) ||
       (int64_t)p.pack_bytes >= (1ll << 31))
     return SB_ERR_UNSUPPORTED;
+  if (split_takes(dtype, N, Cin, H, W, Cout))
+    return conv_split(dgrad, N, Cin, H, W, Cout, in, wt, bias, mask, out, ws, ws_bytes, relu,
+                      prepacked, st, pool_idx);
   const size_t part_off = prepacked ? 0 : p.part_off;
   const size_t need = prepacked ? p.ws_bytes - p.part_off : p.ws_bytes;
   if (need && (ws == nullptr || ws_bytes < need)) return SB_ERR_WORKSPACE;

@@ -506,7 +506,8 @@ namespace sbh {
 // Whether an fp32 pass runs here; the fp32-MFMA kernels of conv_igemm.hip take
 // the others.  Never: images narrower than 4 (2x2 kernels skip the 56 % of the
 // products that are padding), 16 input channels or fewer (a chunk is 32), wide
-// images of 16 output channels or fewer (a tile is 64).  Otherwise by work, as
+// images of 16 output channels or fewer (a tile is 64), sizes whose offsets
+// pass 2^31 bytes.  Otherwise by work, as
 // a block needs about 12 us for a tile of one chunk and the chip 256 of them:
 // with v = pixels x Cin x Cout, from 4e7 on, or from 1.2e7 on where at least
 // 6144 pixels make enough tiles.  Forward and data gradient in us, on the fp32
@@ -516,6 +517,12 @@ namespace sbh {
 // 20 -> 64, 100 images (1.3e7, 10000 pixels) 65, 45.
 bool conv_split_takes(int N, int Cin, int H, int W, int Cout) {
   if (W < 4 || Cin <= 16 || (W >= 32 && Cout <= 16)) return false;
+  // 32-bit offsets: the filters of a wave's four channel blocks, and an image
+  // up to the end of its last chunk of channels.
+  const int64_t nchunks = sb::cdiv(Cin, 32);
+  if (4 * nchunks * sb::kSplitSlice * (int64_t)sizeof(sb::u16) >= (1ll << 31) ||
+      (nchunks * 32 + 8) * H * W * 4 >= (1ll << 31))
+    return false;
   const double px = (double)N * H * W, v = px * Cin * Cout;
   return v >= 4e7 || (W >= 8 && px >= 6144 && v >= 1.2e7);
 }

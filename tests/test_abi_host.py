@@ -43,6 +43,34 @@ def _raw(name, *args):
 P = 0x10000000          # fake device addresses: never dereferenced (calls fail validation)
 
 
+@pytest.mark.parametrize("pass_", [sb.SB_PASS_FWD, sb.SB_PASS_BWD_DATA])
+@pytest.mark.parametrize("image,reduce,out", [((4, 4, 4), 1300000, 64), ((4, 8, 8), 1000000, 64),
+                                              ((16, 4, 4), 110000, 2048)])
+def test_filters_past_the_index_range_are_refused(pass_, image, reduce, out):
+    """Packed filters of 2^31 bytes and more (the first: 3.0e9; over four
+    16-channel blocks of three bf16 parts 4.5e9, past 32 bits) are refused
+    whichever kernel the sizes would take."""
+    n, h, w = image
+    c, k = (reduce, out) if pass_ == sb.SB_PASS_FWD else (out, reduce)
+    d = sb.conv_desc(n, c, h, w, k)
+    need = sb.sb_conv3x3_workspace_bytes(d, pass_)
+    src, wt, dst, ws = P, P + (1 << 36), P + (2 << 36), P + (3 << 36)
+    if pass_ == sb.SB_PASS_FWD:
+        r = _raw("sb_conv3x3_fwd", ctypes.byref(d), src, wt, None, dst, ws, need, None)
+    else:
+        r = _raw("sb_conv3x3_bwd_data", ctypes.byref(d), src, wt, None, dst, ws, need, None)
+    assert r == sb.SB_ERR_UNSUPPORTED
+
+
+def test_offsets_past_the_split_range_take_the_fp32_mfma():
+    # Four channel blocks' filters as bf16 triples pass 2^31 bytes from 621,376
+    # input channels on; an image's last chunk of channels at 2^29 floats.
+    for c, k, h, w, want in ((621376, 64, 4, 4, True), (621408, 64, 4, 4, False),
+                             (60, 64, 2048, 3600, True), (60, 64, 2048, 3700, False)):
+        s = sb.sb_conv3x3_plan_string(sb.conv_desc(1, c, h, w, k), sb.SB_PASS_FWD)
+        assert ("conv3x3_split_f32" in s) == want, s
+
+
 def test_conv_argument_validation():
     d = sb.conv_desc(2, 3, 8, 8, 4)
     bad = [sb.conv_desc(0, 3, 8, 8, 4), sb.conv_desc(2, -1, 8, 8, 4), sb.conv_desc(2, 3, 8, 8, 0),
