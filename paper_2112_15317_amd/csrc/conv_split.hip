@@ -63,7 +63,8 @@ struct STile {
   static constexpr int EP = BM + 4, COPY = BN * EP;
   static constexpr size_t LDS_STAGE = 2 * (size_t)BUF * sizeof(u16);
   static constexpr size_t LDS_OUT = (size_t)WK * COPY * sizeof(float);
-  static constexpr size_t LDS_BYTES = LDS_STAGE > LDS_OUT ? LDS_STAGE : LDS_OUT;
+  static constexpr size_t LDS_REDO = LDS_STAGE > LDS_OUT ? LDS_STAGE : LDS_OUT;
+  static constexpr size_t LDS_BYTES = LDS_REDO + 16;       // behind them the redo flag
   static_assert(LDS_BYTES <= 160 * 1024, "one block per CU");
   __host__ __device__ static constexpr int hp(int img, int hy, int hx) {
     return (img * HH + hy) * HW + hx;
@@ -71,24 +72,71 @@ struct STile {
 };
 constexpr int kSThreads = 512;
 
-// One output in plain fp32 from the operands, over the channels [c0, c1).
-__device__ __forceinline__ float conv_one(const ConvArgs& a, int n, int co, int h, int w, int c0,
-                                          int c1) {
-  const u16* wp = (const u16*)a.wpk + (size_t)(co >> 4) * a.nchunks * kSplitSlice + (co & 15) * 8;
-  const float* x = (const float*)a.in + (size_t)n * a.Cin * a.H * a.W;
-  float s = 0.f;
+// The block's output tile on the fp32 MFMA, over the channels [c0, c1), for
+// blocks that the split cannot carry: operands straight from memory (the
+// filters put together from their parts), each tap's sum added only where the
+// tap is inside the image.  Writes copy 0 of E, and zeros to the others.
+template <class T>
+__device__ __forceinline__ void conv_tile_f32(const ConvArgs& a, float* E, int n0, int h0, int w0,
+                                              int co0, int c0, int c1, int wave, int lane) {
+  const int lr = lane & 15, lq = lane >> 4;
+  constexpr int CB = T::BM / 16;
+  const int HWs = a.H * a.W, cblk = cdiv(a.Cout, 16);
 #pragma unroll 1
-  for (int c = c0; c < c1; ++c) {
-    const u16* wc = wp + (size_t)(c >> 5) * kSplitSlice + ((c >> 3) & 3) * 128 + (c & 7);
+  for (int q = wave; q < T::WN * CB; q += kSThreads / 64) {     // 64 channels x 16 pixels
+    const int g = q / CB, px = q % CB * 16 + lr;
+    const int n = n0 + px / (T::TH * T::TW), h = h0 + px / T::TW % T::TH, w = w0 + px % T::TW;
+    const float* x = (const float*)a.in + (size_t)min(n, a.N - 1) * a.Cin * HWs;
+    const u16* wp[4];
+    f4 acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int blk = min(co0 / 16 + g * 4 + i, cblk - 1);
+      wp[i] = (const u16*)a.wpk + (size_t)blk * a.nchunks * kSplitSlice + lr * 8;
+      acc[i] = f4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll 1
     for (int t = 0; t < 9; ++t) {
       const int hh = h + t / 3 - 1, ww = w + t % 3 - 1;
-      if ((unsigned)hh >= (unsigned)a.H || (unsigned)ww >= (unsigned)a.W) continue;
-      const u16* q = wc + t * 3 * 512;
-      s = fmaf(x[((size_t)c * a.H + hh) * a.W + ww], split_value(q[0], q[512], q[1024]), s);
+      const bool ok = n < a.N && (unsigned)hh < (unsigned)a.H && (unsigned)ww < (unsigned)a.W;
+      f4 c[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+      for (int ch = c0; ch < c1; ch += 32) {       // a lane's channels: 8 lq .. + 7 of the chunk
+        const int k = ch + lq * 8;
+        const float* xk = x + (size_t)k * HWs + hh * a.W + ww;
+        const size_t o = (size_t)(ch >> 5) * kSplitSlice + t * 3 * 512 + lq * 128;
+        s8 f[4][3];
+        float b[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int p = 0; p < 3; ++p) f[i][p] = *reinterpret_cast<const s8*>(wp[i] + o + p * 512);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b[j] = ok && k + j < c1 ? xk[(size_t)j * HWs] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            c[i] = mfma16x16x4(
+                split_value((u16)f[i][0][j], (u16)f[i][1][j], (u16)f[i][2][j]), b[j], c[i]);
+      }
+      if (ok) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += c[i];
+      }
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float* e = E + (g * 64 + i * 16 + 4 * lq + v) * T::EP + px;
+        e[0] = acc[i][v];
+#pragma unroll
+        for (int k = 1; k < T::WK; ++k) e[k * T::COPY] = 0.f;
+      }
   }
-  return s;
 }
 
 // POOL (forward, unsplit): ReLU and 2x2 max pooling run on the output tile
@@ -118,6 +166,8 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
   const int HWs = a.H * a.W;
   const int nt = cdiv(kc1 - kc0, T::WK);           // rounds: a chunk per wave group
   float* E = reinterpret_cast<float*>(ldsu);
+  int* redo = reinterpret_cast<int*>(ldsu + T::LDS_REDO / sizeof(u16));
+  if (tid == 0) *redo = 0;
 
   if (wave >= 4) {
     // ---- staging waves ----
@@ -271,6 +321,7 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
     if (t < nt) round(std::integral_constant<int, 0>{}, t);
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i][3] += cp[i];
+    if (split_suspect(acc)) *redo = 1;
     // acc[i][j] element v: channel wn*64 + i*16 + 4*lq + v, pixel wm*64 + j*16 + lr.
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -285,7 +336,10 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
   // ---- the tile leaves through LDS: WK copies of [channel][pixel], pixels
   // image-major, added in group order ----
   __syncthreads();
-  const int c_lo = kc0 * 32, c_hi = min(a.Cin, kc1 * 32);
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(*redo), 0)) {
+    conv_tile_f32<T>(a, E, n0, h0, w0, co0, kc0 * 32, min(a.Cin, kc1 * 32), wave, lane);
+    __syncthreads();
+  }
   if constexpr (POOL) {
     // Pooled pixel q = (channel, image, pooled row, pooled column), columns
     // fastest: the first maximum in row-major window order wins (strict >),
@@ -309,8 +363,6 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
         float s = lk[0];
 #pragma unroll
         for (int g = 1; g < T::WK; ++g) s += lk[g * T::COPY];
-        if (__builtin_expect(split_suspect(s), 0))
-          s = conv_one(a, n, co, 2 * oh + (k >> 1), 2 * ow + (k & 1), c_lo, c_hi);
         v[k] = s + bv;
       }
       float m = v[0];
@@ -343,15 +395,6 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
     for (int g = 1; g < T::WK; ++g)
       v += *reinterpret_cast<const f4*>(E + g * T::COPY + col * T::EP + px);
     const int h = h0 + rem / T::TW, w = w0 + rem % T::TW;
-    if (__builtin_expect(split_suspect(v[0]) || split_suspect(v[1]) || split_suspect(v[2]) ||
-                             split_suspect(v[3]), 0)) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int he = h0 + (rem + e) / T::TW, we = w0 + (rem + e) % T::TW;
-        if (split_suspect(v[e]) && he < a.H && we < a.W)
-          v[e] = conv_one(a, n, co, he, we, c_lo, c_hi);
-      }
-    }
     const size_t base = ((size_t)n * a.Cout + co) * HWs;
     const float bv = !part && a.bias ? a.bias[co] : 0.f;
     if (vec) {

@@ -78,7 +78,8 @@ struct WsTile {
   static constexpr int RP = BC * 9 + 4, COPY = BK * RP;
   static constexpr size_t LDS_STAGE = 2 * (size_t)BUF * sizeof(u16);
   static constexpr size_t LDS_OUT = (4 * COPY + 64) * sizeof(float);
-  static constexpr size_t LDS_BYTES = LDS_STAGE > LDS_OUT ? LDS_STAGE : LDS_OUT;
+  static constexpr size_t LDS_REDO = LDS_STAGE > LDS_OUT ? LDS_STAGE : LDS_OUT;
+  static constexpr size_t LDS_BYTES = LDS_REDO + 16;   // behind them the redo flag
   static_assert(LDS_BYTES <= 160 * 1024, "one block per CU");
   __host__ __device__ static constexpr int hp(int p) {   // halo pixel of tile pixel p at tap (0, 0)
     return (p / (TH * TW) * HH + p / TW % TH) * HW + p % TW;
@@ -94,27 +95,60 @@ __device__ __forceinline__ s8 tr8(const u16* lo, const u16* hi) {
   return s8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 }
 
-// One element of dw in plain fp32 over the pixel tiles [pt0, pt1).
+// The block's output on the fp32 MFMA, over the pixel tiles [pt0, pt1), for
+// blocks that the split cannot carry: operands straight from memory, a pixel
+// taking part in a tap only where both are inside the image.  Wave w has 16 k
+// (w % 4) and every second tile; a lane has 4 consecutive pixels of a row and
+// the 3 x 6 window of x around them.  Writes copies 0 and 2 of E, which are
+// added, and zeros to the others.
 template <class T>
-__device__ __forceinline__ float wgrad_one(const WsArgs& a, int k, int c, int tap, int pt0,
-                                           int pt1) {
-  float s = 0.f;
+__device__ __forceinline__ void wgrad_tile_f32(const WsArgs& a, float* E, int k0, int c0, int pt0,
+                                               int pt1, int wave, int lane) {
+  const int lr = lane & 15, lq = lane >> 4;
+  const int k = k0 + (wave & 3) * 16 + lr, c = c0 + lr;
+  const int HWs = a.H * a.W;
+  f4 acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-  for (int pt = pt0; pt < pt1; ++pt) {
+  for (int pt = pt0 + (wave >> 2); pt < pt1; pt += 2) {
     const int tx = pt % a.tiles_w, ty = pt / a.tiles_w % a.tiles_h, tn = pt / a.tiles_w / a.tiles_h;
-#pragma unroll 1
-    for (int p = 0; p < T::BP; ++p) {
+#pragma unroll 2
+    for (int q = 0; q < T::BP; q += 16) {
+      const int p = q + lq * 4;
       const int n = tn * T::IMGS + p / (T::TH * T::TW);
       const int h = ty * T::TH + p / T::TW % T::TH, w = tx * T::TW + p % T::TW;
-      const int hh = h + tap / 3 - 1, ww = w + tap % 3 - 1;
-      if (n >= a.N || h >= a.H || w >= a.W || (unsigned)hh >= (unsigned)a.H ||
-          (unsigned)ww >= (unsigned)a.W)
-        continue;
-      s = fmaf(a.x[(((size_t)n * a.C + c) * a.H + hh) * a.W + ww],
-               a.dy[(((size_t)n * a.K + k) * a.H + h) * a.W + w], s);
+      const bool in = n < a.N && h < a.H;
+      const float* dp = a.dy + ((size_t)n * a.K + k) * HWs + h * a.W + w;
+      const float* xp = a.x + ((size_t)n * a.C + c) * HWs + h * a.W + w;
+      float d[4], x[3][6];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] = in && w + e < a.W && k < a.K ? dp[e] : 0.f;
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int e = 0; e < 6; ++e)
+          x[r][e] = in && c < a.C && (unsigned)(h + r - 1) < (unsigned)a.H &&
+                            (unsigned)(w + e - 1) < (unsigned)a.W
+                        ? xp[(r - 1) * a.W + e - 1] : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          const bool ok = in && w + e < a.W && (unsigned)(h + t / 3 - 1) < (unsigned)a.H &&
+                          (unsigned)(w + e + t % 3 - 1) < (unsigned)a.W;
+          acc[t] = mfma16x16x4(ok ? d[e] : 0.f, ok ? x[t / 3][e + t % 3] : 0.f, acc[t]);
+        }
     }
   }
-  return s;
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float* e = E + (wave >> 2) * 2 * T::COPY + ((wave & 3) * 16 + 4 * lq + v) * T::RP + lr * 9 + t;
+      e[0] = acc[t][v];
+      e[T::COPY] = 0.f;
+    }
 }
 
 // VEC: rows are whole aligned quads (W a multiple of 4, 16-byte tensors), so a
@@ -134,6 +168,8 @@ __device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
   const bool do_db = a.db != nullptr && ct == 0;
   const int HWs = a.H * a.W;
   const size_t wsz = (size_t)a.K * a.C * 9;
+  int* redo = reinterpret_cast<int*>(ldsu + T::LDS_REDO / sizeof(u16));
+  if (tid == 0) *redo = 0;
 
   if (wave >= 4) {
     // ---- staging waves ----
@@ -305,6 +341,7 @@ __device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i][8] += cp[i];
+    if (split_suspect(acc)) *redo = 1;
     // acc[i][t] element v: row i*16 + 4*lq + v, channel lr, tap t.
     float* R = E + wave * T::COPY;
 #pragma unroll
@@ -315,6 +352,10 @@ __device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
         for (int v = 0; v < 4; ++v) R[(i * 16 + 4 * lq + v) * T::RP + lr * 9 + t] = acc[i][t][v];
   }
   __syncthreads();
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(*redo), 0)) {
+    wgrad_tile_f32<T>(a, E, k0, c0, pt0, pt1, wave, lane);
+    __syncthreads();
+  }
 
   // ---- the block's 64 k x (16 c x 9 taps), rows contiguous in dw ----
   float* dst = a.splits == 1 ? a.dw : a.part + (size_t)split * (wsz + a.K);
@@ -332,13 +373,6 @@ __device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
       const f4 u = *reinterpret_cast<const f4*>(E + w * T::COPY + row * T::RP + col);
       if (w & 1) v -= u;
       else v += u;
-    }
-    if (__builtin_expect(split_suspect(v[0]) || split_suspect(v[1]) || split_suspect(v[2]) ||
-                             split_suspect(v[3]), 0)) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (split_suspect(v[e]) && col + e < cw)
-          v[e] = wgrad_one<T>(a, k, c0 + (col + e) / 9, (col + e) % 9, pt0, pt1);
     }
     float* o = dst + (size_t)k * a.C * 9 + (size_t)c0 * 9 + col;
     if (vec) {

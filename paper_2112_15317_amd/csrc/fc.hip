@@ -70,7 +70,8 @@ struct GemmTile {
   static constexpr int EP = BN + 4;                         // output tile row pitch (floats)
   static constexpr size_t LDS_STAGES = 3 * (size_t)STAGE * sizeof(u16);
   static constexpr size_t LDS_OUT = ((size_t)BM * EP + BN * KO) * sizeof(float);
-  static constexpr size_t LDS_BYTES = LDS_STAGES > LDS_OUT ? LDS_STAGES : LDS_OUT;
+  static constexpr size_t LDS_REDO = LDS_STAGES > LDS_OUT ? LDS_STAGES : LDS_OUT;
+  static constexpr size_t LDS_BYTES = LDS_REDO + 16;        // behind them the redo flag
   static_assert(LDS_BYTES <= 160 * 1024, "one block per CU");
 };
 
@@ -195,20 +196,38 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& g, int& mtile, int& n
   ntile = t - mtile * g.nt;
 }
 
-// One output in plain fp32, over k in [k0, k1).
-template <bool A_KC, bool B_KC, class E>
-__device__ __forceinline__ float gemm_one(const GemmArgs& g, int m, int n, int k0, int k1) {
-  float s = 0.f;
-#pragma unroll 1
-  for (int k = k0; k < k1; ++k) {
+// The block's output tile on the fp32 MFMA, over k in [k0, k1), for blocks
+// that the split cannot carry: operands straight from memory.  A wave has 16
+// rows and BM * BN / 2048 blocks of 16 columns.
+template <class T, bool A_KC, bool B_KC, bool AMK, bool BMK>
+__device__ __forceinline__ void gemm_tile_f32(const GemmArgs& g, float* O, int m0, int n0, int k0,
+                                              int k1, int wave, int lane) {
+  constexpr int RBT = T::BM / 16, NB = T::BM * T::BN / 2048;
+  const int lr = lane & 15, lq = lane >> 4;
+  const int rb = wave % RBT, cb = wave / RBT * NB, m = m0 + rb * 16 + lr;
+  const float *A = (const float*)g.a, *B = (const float*)g.b;
+  const float *MA = (const float*)g.amask, *MB = (const float*)g.bmask;
+  f4 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) acc[j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int kk = k0; kk < k1; kk += 4) {
+    const int k = kk + lq;
     const size_t ao = A_KC ? (size_t)m * g.lda + k : (size_t)k * g.lda + m;
-    const size_t bo = B_KC ? (size_t)n * g.ldb + k : (size_t)k * g.ldb + n;
-    float av = Elem<E>::load((const E*)g.a, ao), bv = Elem<E>::load((const E*)g.b, bo);
-    if (g.amask && !(Elem<E>::load((const E*)g.amask, ao) > 0.f)) av = 0.f;
-    if (g.bmask && !(Elem<E>::load((const E*)g.bmask, bo) > 0.f)) bv = 0.f;
-    s = fmaf(av, bv, s);
+    const bool aok = m < g.M && k < k1 && (!AMK || MA[ao] > 0.f);
+    const float av = aok ? A[ao] : 0.f;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int n = n0 + (cb + j) * 16 + lr;
+      const size_t bo = B_KC ? (size_t)n * g.ldb + k : (size_t)k * g.ldb + n;
+      const bool bok = n < g.N && k < k1 && (!BMK || MB[bo] > 0.f);
+      acc[j] = mfma16x16x4(av, bok ? B[bo] : 0.f, acc[j]);
+    }
   }
-  return s;
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) O[(rb * 16 + 4 * lq + v) * T::EP + (cb + j) * 16 + lr] = acc[j][v];
 }
 
 template <class T, bool A_KC, bool B_KC, bool VEC, class E, class CE, bool AMK, bool BMK>
@@ -225,6 +244,8 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
   const int ke = min(g.K, kb + g.k_per_split);
   const int nk = ke > kb ? cdiv(ke - kb, KS) : 0;
   const bool do_colsum = g.colsum != nullptr && mtile == 0;
+  int* redo = reinterpret_cast<int*>(ldsu + T::LDS_REDO / sizeof(u16));
+  if (tid == 0) *redo = 0;
 
   if (wave >= 4) {
     // ---- staging waves ----
@@ -369,6 +390,7 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
     if (t < nk) stage(std::integral_constant<int, 0>{}, t);
 #pragma unroll
     for (int i = 0; i < T::RB; ++i) acc[i][T::CB - 1] += cp[i];
+    if (T::NP == 3 && split_suspect(acc)) *redo = 1;
     // acc[i][j] element v: row wm*BM/2 + 16 i + 4 lq + v, column wn*BN/2 + 16 j + lr.
 #pragma unroll
     for (int i = 0; i < T::RB; ++i)
@@ -380,6 +402,12 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
               acc[i][j][v];
   }
   __syncthreads();
+  if constexpr (T::NP == 3) {                      // bf16 products are exact
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(*redo), 0)) {
+      gemm_tile_f32<T, A_KC, B_KC, AMK, BMK>(g, O, m0, n0, kb, ke, wave, lane);
+      __syncthreads();
+    }
+  }
 
   if (do_colsum && tid < T::BN && n0 + tid < g.N) {
     float s = 0.f;
@@ -400,12 +428,6 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
     const int m = m0 + r, n = n0 + c;
     if (m >= g.M || n >= g.N) continue;
     f4 v = *reinterpret_cast<const f4*>(O + r * T::EP + c);
-    if (__builtin_expect(split_suspect(v[0]) || split_suspect(v[1]) || split_suspect(v[2]) ||
-                             split_suspect(v[3]), 0)) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (split_suspect(v[e]) && n + e < g.N) v[e] = gemm_one<A_KC, B_KC, E>(g, m, n + e, kb, ke);
-    }
     const size_t o = (size_t)m * g.ldc + n;
     if (!partial) {
 #pragma unroll

@@ -21,10 +21,11 @@
 //
 // Values the triple cannot carry.  An infinite or NaN operand, or one that
 // rounds to infinity (above 3.39e38), makes a NaN of every sum it enters; an
-// operand below 2^-110 loses low bits to the bf16 range.  The kernels
-// therefore look at each result (split_suspect) and recompute one that is
-// not finite, or nonzero and below 2^-100, in plain fp32 from the original
-// operands, so infinities, NaNs and tiny values come out as from fp32 sums.
+// operand below 2^-110 loses low bits to the bf16 range.  A block whose sums
+// are not all finite, or some nonzero and below 2^-100 (split_suspect), redoes
+// its output tile on the fp32 MFMA from the operands in memory, so infinities,
+// NaNs and tiny values come out as from fp32 sums, at 3 to 5 times the block's
+// time.
 #pragma once
 
 #include "sb_internal.hpp"
@@ -94,11 +95,21 @@ __device__ __forceinline__ float split_value(u16 h, u16 m, u16 l) {
   return bf16_to_f32(h) + (bf16_to_f32(m) + bf16_to_f32(l));
 }
 
-// Whether a result has to be recomputed: not finite, or nonzero and below
-// 2^-100.
-__device__ __forceinline__ bool split_suspect(float v) {
-  const uint32_t b = __float_as_uint(v) & 0x7fffffffu;
-  return b - 0x0d800000u >= 0x72000000u && b != 0;
+// Whether a wave's sums have to be recomputed: one is not finite, or nonzero
+// and below 2^-100.
+template <int I, int J>
+__device__ __forceinline__ bool split_suspect(const f4 (&acc)[I][J]) {
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < I; ++i)
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const uint32_t b = __float_as_uint(acc[i][j][v]) & 0x7fffffffu;
+        bad |= b - 0x0d800000u >= 0x72000000u && b != 0;
+      }
+  return bad;
 }
 
 }  // namespace sb

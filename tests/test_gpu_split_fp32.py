@@ -215,3 +215,49 @@ def test_fc_against_64_bits(m, ki, ns):
     assert torch.isinf(y).any(1).nonzero().flatten().tolist() == [m // 2]
     bad = ~torch.isfinite(dw).all(1)
     assert bad.nonzero().flatten().tolist() == [ki // 2] and not torch.isfinite(dw[ki // 2]).any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("everywhere", [True, False])
+def test_special_values_cost_a_bounded_time(value, everywhere):
+    # A block that meets such values redoes its tile on the fp32 MFMA: 3 to 7
+    # times an ordinary call on these sizes.  Output by output on the vector
+    # ALU it was 45 to 130 times.
+    print_case("split special cost", value=value, everywhere=everywhere)
+
+    def best(f):
+        ms = []
+        for _ in range(4):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            f()
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        return min(ms)
+
+    def fill(t):
+        (t if everywhere else t.view(-1)[:1]).fill_(value)
+
+    n, c, h, w, k = 128, 64, 32, 32, 64
+    d = sb.conv_desc(n, c, h, w, k, sb.SB_F32)
+    ws = _ws(max(sb.sb_conv3x3_workspace_bytes(d, p) for p in PASSES))
+    x, wt, b, dy = (_dev(t) for t in _inputs((n, c, h, w, k)))
+    y, dx, dw, db = (torch.empty_like(t) for t in (dy, x, wt, b))
+    m, ki, ns = 512, 4096, 1024
+    fd = sb.fc_desc(m, ki, ns, sb.SB_F32)
+    fws = _ws(max(sb.sb_fc_workspace_bytes(fd, p) for p in (sb.SB_FC_FWD, sb.SB_FC_BWD)))
+    fx, fw, fdy = (_dev(_rand(*s, seed=9)) for s in ((m, ki), (ki, ns), (m, ns)))
+    fy, fdx, fdw = (torch.empty_like(t) for t in (fdy, fx, fw))
+    calls = [lambda: sb.sb_conv3x3_fwd(d, x, wt, b, y, ws),
+             lambda: sb.sb_conv3x3_bwd_data(d, dy, wt, None, dx, ws),
+             lambda: sb.sb_conv3x3_bwd_weight(d, x, dy, dw, db, ws),
+             lambda: sb.sb_fc_shard_fwd(fd, fx, fw, None, fy, fws),
+             lambda: sb.sb_fc_shard_bwd(fd, fx, fw, fdy, None, fdx, fdw, None, False, fws)]
+    plain = [best(f) for f in calls]
+    for t in (x, dy, fx, fdy):
+        fill(t)
+    ratios = [best(f) / p for f, p in zip(calls, plain)]
+    print("ratios", ["%.1f" % r for r in ratios])
+    assert max(ratios) < 14, ratios
