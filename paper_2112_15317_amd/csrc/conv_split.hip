@@ -190,6 +190,7 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
     }
     const rsrc_t xr = input_rsrc<float>(a, n0, T::IMGS);
     f8v rx[T::XI];
+    uint32_t lost = 0;
     auto gload = [&](int t) {
       const int cb = t * T::WK * 32;
 #pragma unroll
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
         const int u = ptid + 256 * i;
         if (T::TASKS % 256 != 0 && u >= T::TASKS) continue;
         const int g = u / (4 * T::PLANE), r = u % (4 * T::PLANE);
-        const Split8 s = split8(rx[i]);
+        const Split8 s = split8(rx[i], lost);
 #pragma unroll
         for (int p = 0; p < 3; ++p)
           *reinterpret_cast<s8*>(X + g * T::GROUP + p * T::PART + r * 8) = s.p[p];
@@ -224,6 +225,7 @@ __global__ __launch_bounds__(kSThreads, 2) void conv3x3_split_f32(ConvArgs a) {
       if (t + 2 < nt) gload(t + 2);
       __syncthreads();
     }
+    if (lost & 0xffffu) *redo = 1;
   } else {
     // ---- multiplying waves ----
     const int lr = lane & 15, lq = lane >> 4;

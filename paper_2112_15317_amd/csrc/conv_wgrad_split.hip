@@ -196,6 +196,7 @@ __device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
     const int dch = min(8, a.K - k0 - doct * 8);           // live channels of each task
     const int qch = min(8, a.C - c0 - qoct * 8), ech = min(8, a.C - c0 - eoct * 8);
     f4 rd[8], rq[8];
+    uint32_t lost = 0;
     f8v re, dbs = f8v{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // Quad of channel j at byte offset off (+ j planes): its first `cols`
     // columns are in the image (all or none if VEC).
@@ -239,7 +240,7 @@ __device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
     };
     auto neg = [&](float v) { return __uint_as_float(__float_as_uint(v) ^ dneg); };
     auto put = [&](u16* at, int part, f8v v) {
-      const Split8 s = split8(v);
+      const Split8 s = split8(v, lost);
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<s8*>(at + p * part) = s.p[p];
       __builtin_amdgcn_sched_barrier(0);           // one pixel's parts in registers at a time
@@ -272,6 +273,7 @@ __device__ __forceinline__ void wgrad_split_block(const WsArgs& a, int b) {
       if (t + 2 < nt) gload(t + 2);
       __syncthreads();
     }
+    if (lost & 0xffffu) *redo = 1;
     if (do_db) {
       // The 32 lanes of a channel group hold its pixels.
 #pragma unroll

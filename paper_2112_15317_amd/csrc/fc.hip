@@ -158,8 +158,9 @@ struct GStage {
     load_one(r, k0, ke, v);
     if constexpr (MASK) load_one(rm, k0, ke, m);
   }
-  // Stores the pieces; r0 as in init.  Returns the (masked) values in v.
-  __device__ __forceinline__ void store(u16* S, int r0) {
+  // Stores the pieces; r0 as in init.  Leaves the (masked) values in v; lost as
+  // in split_pair.
+  __device__ __forceinline__ void store(u16* S, int r0, uint32_t& lost) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       if constexpr (MASK) {
@@ -173,7 +174,7 @@ struct GStage {
         for (int e = 0; e < 4; ++e) h[e] = f32x2_to_bf16x2(v[i][2 * e], v[i][2 * e + 1]);
         *reinterpret_cast<s8*>(at) = __builtin_bit_cast(s8, h);
       } else {
-        const Split8 s = split8(v[i]);
+        const Split8 s = split8(v[i], lost);
 #pragma unroll
         for (int p = 0; p < 3; ++p) *reinterpret_cast<s8*>(at + p * PART) = s.p[p];
       }
@@ -261,6 +262,7 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
     GStage<T::BN, T::KO, T::BPL, T::BPART, T::NP, B_KC, VEC, E, BMK> sb_;
     sa.init(g.lda, g.M, m0, ptid);
     sb_.init(g.ldb, g.N, n0, ptid);
+    uint32_t lost = 0;
     float cs[2] = {0.f, 0.f};                      // column sums of this lane's two rows of B
     auto add_cols = [&](const auto& q) {
 #pragma unroll
@@ -274,8 +276,8 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
     };
     auto store = [&](int t) {
       u16* S = ldsu + t % 3 * T::STAGE;
-      sa.store(S, m0);
-      sb_.store(S + T::LDS_A, n0);
+      sa.store(S, m0, lost);
+      sb_.store(S + T::LDS_A, n0, lost);
       if (!B_KC && do_colsum) add_cols(sb_);
     };
     if (nk > 1) {                                  // both loads in flight at once
@@ -284,8 +286,8 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
       sa0.load(ra, ram, kb, ke);
       sb0.load(rb, rbm, kb, ke);
       load(1);
-      sa0.store(ldsu, m0);
-      sb0.store(ldsu + T::LDS_A, n0);
+      sa0.store(ldsu, m0, lost);
+      sb0.store(ldsu + T::LDS_A, n0, lost);
       if (!B_KC && do_colsum) add_cols(sb0);
       store(1);
     } else {
@@ -299,6 +301,7 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
       if (t + 3 < nk) load(t + 3);
       __syncthreads();
     }
+    if (T::NP == 3 && (lost & 0xffffu)) *redo = 1;
     if (!B_KC && do_colsum) {                      // [octet][row] after the output tile
 #pragma unroll
       for (int i = 0; i < 2; ++i) O[T::BM * T::EP + sb_.oct[i] * T::BN + sb_.row[i] - n0] = cs[i];

@@ -20,12 +20,13 @@
 // and 1.80 when consecutive MFMAs share an operand.
 //
 // Values the triple cannot carry.  An infinite or NaN operand, or one that
-// rounds to infinity (above 3.39e38), makes a NaN of every sum it enters; an
-// operand below 2^-110 loses low bits to the bf16 range.  A block whose sums
-// are not all finite, or some nonzero and below 2^-100 (split_suspect), redoes
-// its output tile on the fp32 MFMA from the operands in memory, so infinities,
-// NaNs and tiny values come out as from fp32 sums, at 3 to 5 times the block's
-// time.
+// rounds to infinity (above 3.39e38), makes a NaN of every sum it enters.  bf16
+// ends at 2^-133 (the MFMA keeps subnormals, of operands, products and sums), so
+// an operand below 2^-110 may have bits that no part holds; they are left in
+// the remainder after the third part, whose low 16 bits are zero otherwise.  A
+// block whose sums are not all finite, or whose operands lose bits, redoes its
+// output tile on the fp32 MFMA from the operands in memory, so infinities, NaNs
+// and tiny values come out as from fp32 sums, at 3 to 7 times the call's time.
 #pragma once
 
 #include "sb_internal.hpp"
@@ -54,62 +55,62 @@ struct Split8 { s8 p[3]; };   // high, mid, low
 // The triples of two values, packed as bf16 pairs (lo in bits 0..15).  (The
 // remainders as bf16 pair dot products with (-1, 0) and (0, -1) would be 7
 // instructions instead of 11, but those run slower: FC products 35 -> 38 us.)
+// lost: low 16 bits set if a value has bits below 2^-133.
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m,
-                                           uint32_t& l) {
+                                           uint32_t& l, uint32_t& lost) {
   h = f32x2_to_bf16x2(a, b);
   float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
   m = f32x2_to_bf16x2(ra, rb);
   ra -= __uint_as_float(m << 16);
   rb -= __uint_as_float(m & 0xffff0000u);
   l = f32x2_to_bf16x2(ra, rb);
+  lost |= __float_as_uint(ra) | __float_as_uint(rb);
 }
 
-__device__ __forceinline__ Split8 split8(f8v v) {
+__device__ __forceinline__ Split8 split8(f8v v, uint32_t& lost) {
   u32x4 h, m, l;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t a, b, c;
-    split_pair(v[2 * j], v[2 * j + 1], a, b, c);
+    split_pair(v[2 * j], v[2 * j + 1], a, b, c, lost);
     h[j] = a; m[j] = b; l[j] = c;
   }
   return Split8{{__builtin_bit_cast(s8, h), __builtin_bit_cast(s8, m), __builtin_bit_cast(s8, l)}};
 }
 
 // The triple of a stored operand, from which split_value gets the value back
-// exactly: a value whose high part would round to infinity is cut to bf16
-// instead of rounded, an infinity or NaN is its own high part with zeros.
+// exactly.  A value that the triple cannot carry is stored as a NaN, so that
+// every sum it enters asks for the fp32 MFMA, and its own bits.
+constexpr u16 kSplitRaw = 0x7fff;
 __device__ __forceinline__ void split_stored(float v, u16& h, u16& m, u16& l) {
-  const uint32_t bits = __float_as_uint(v);
-  if ((bits & 0x7f800000u) == 0x7f800000u) {
-    h = (u16)((bits >> 16) | ((bits & 0x7fffffu) ? 0x40u : 0u));
-    m = l = 0;
-    return;
-  }
   h = f32_to_bf16(v);
-  if ((h & 0x7f80u) == 0x7f80u) h = (u16)(bits >> 16);
   const float r = v - bf16_to_f32(h);
   m = f32_to_bf16(r);
-  l = f32_to_bf16(r - bf16_to_f32(m));
+  const float q = r - bf16_to_f32(m);
+  l = f32_to_bf16(q);
+  if ((h & 0x7f80u) == 0x7f80u || (__float_as_uint(q) & 0xffffu)) {
+    const uint32_t bits = __float_as_uint(v);
+    h = kSplitRaw;
+    m = (u16)(bits >> 16);
+    l = (u16)bits;
+  }
 }
 __device__ __forceinline__ float split_value(u16 h, u16 m, u16 l) {
-  return bf16_to_f32(h) + (bf16_to_f32(m) + bf16_to_f32(l));
+  return h == kSplitRaw ? __uint_as_float((uint32_t)m << 16 | l)
+                        : bf16_to_f32(h) + (bf16_to_f32(m) + bf16_to_f32(l));
 }
 
-// Whether a wave's sums have to be recomputed: one is not finite, or nonzero
-// and below 2^-100.
+// Whether a wave's sums are not all finite.
 template <int I, int J>
 __device__ __forceinline__ bool split_suspect(const f4 (&acc)[I][J]) {
-  bool bad = false;
+  float z[4] = {0.f, 0.f, 0.f, 0.f};               // stays 0 over finite values
 #pragma unroll
   for (int i = 0; i < I; ++i)
 #pragma unroll
     for (int j = 0; j < J; ++j)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const uint32_t b = __float_as_uint(acc[i][j][v]) & 0x7fffffffu;
-        bad |= b - 0x0d800000u >= 0x72000000u && b != 0;
-      }
-  return bad;
+      for (int v = 0; v < 4; ++v) z[v] = fmaf(acc[i][j][v], 0.f, z[v]);
+  return !((z[0] + z[1]) + (z[2] + z[3]) == 0.f);
 }
 
 }  // namespace sb

@@ -217,6 +217,87 @@ def test_fc_against_64_bits(m, ki, ns):
     assert bad.nonzero().flatten().tolist() == [ki // 2] and not torch.isfinite(dw[ki // 2]).any()
 
 
+# Scales of x, w and dy: small operands that meet large ones, so that their
+# products are ordinary numbers (sums of 1e4 products of 2^108 stay below 2^117);
+# 2^-140 against 1, whose products are subnormal.
+SMALL = [(-118, 24, 24), (24, -118, 24), (24, 24, -118), (-140, 100, 8), (8, -140, 100),
+         (100, 8, -140), (-140, 0, 0), (0, -140, 0), (0, 0, -140)]
+
+
+def _scaled(t, e, rows=None):
+    """t * 2^e in fp32 (exact but for subnormal results), all of it or its rows of dim 1."""
+    if rows is None:
+        return (t.double() * 2.0 ** e).float()
+    t = t.clone()
+    t[:, rows] = (t[:, rows].double() * 2.0 ** e).float()
+    return t
+
+
+def _small_ok(name, a, r, e, terms):
+    """Products of 2^e (times the inputs' own sizes), fp32 sums of `terms`
+    roundings; below 2^-100 every product may be off by half of the last
+    subnormal bit, 2^-150 (the filters of 400 channels are about 2^-6)."""
+    err = (a.double() - r).norm() / r.norm()
+    bound = (terms / 2) ** 0.5 * 2.0 ** -24 + (2.0 ** (-145 - e) if e < -100 else 0.0)
+    assert torch.isfinite(a).all() and err < bound, (name, float(err), bound)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("exps", SMALL, ids=str)
+@pytest.mark.parametrize("shape", [(24, 64, 16, 16, 64), (40, 80, 4, 4, 800), (36, 72, 30, 8, 20)])
+def test_conv_small_operands_keep_their_bits(shape, exps):
+    print_case("split conv small operands", shape=shape, exps=exps)
+    ex, ew, ed = exps
+    x, w, b, dy = _inputs(shape)
+    x, w, dy, b = _scaled(x, ex), _scaled(w, ew), _scaled(dy, ed), torch.zeros_like(b)
+    got, ref = _run(shape, x, w, b, dy), _ref(x, w, b, dy)
+    # The filters' own size is about 1 / (3 sqrt(c)).
+    for name, a, r, e in zip(("y", "dx", "dw"), got, ref, (ex + ew, ed + ew, ex + ed)):
+        _small_ok(name, a, r, e, 7200)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,ki,ns", [(65, 130, 130), (512, 512, 1024)])
+@pytest.mark.parametrize("exps", SMALL, ids=str)
+def test_fc_small_operands_keep_their_bits(m, ki, ns, exps):
+    print_case("split fc small operands", m=m, ki=ki, ns=ns, exps=exps)
+    ex, ew, ed = exps
+    x, w, dy = (_scaled(_rand(*s, seed=i), e) for i, (s, e) in
+                enumerate((((m, ki), ex), ((ki, ns), ew), ((m, ns), ed))))
+    d = sb.fc_desc(m, ki, ns, sb.SB_F32)
+    ws = _ws(max(sb.sb_fc_workspace_bytes(d, p) for p in (sb.SB_FC_FWD, sb.SB_FC_BWD)))
+    y, dx, dw = (torch.full_like(t, 7.0, device="cuda") for t in (dy, x, w))
+    sb.sb_fc_shard_fwd(d, _dev(x), _dev(w), None, y, ws)
+    sb.sb_fc_shard_bwd(d, _dev(x), _dev(w), _dev(dy), None, dx, dw, None, False, ws)
+    torch.cuda.synchronize()
+    x, w, dy = x.double(), w.double(), dy.double()
+    for name, a, r, e in (("y", y, x @ w, ex + ew), ("dx", dx, dy @ w.T, ed + ew),
+                          ("dw", dw, x.T @ dy, ex + ed)):
+        _small_ok(name, a.cpu(), r, e, 1024)
+
+
+@pytest.mark.gpu
+def test_a_few_small_operands_among_ordinary_ones():
+    # One channel of 2^-120 against filters (and dy) of 2^120: as large in every
+    # sum as the others.
+    shape = (24, 64, 16, 16, 64)
+    print_case("split conv few small operands", shape=shape)
+    x, w, b, dy = _inputs(shape)
+    x1, w1 = _scaled(x, -120, [5]), _scaled(w, 120, [5])
+    y = _run(shape, x1, w1, torch.zeros_like(b), dy)[0]
+    assert rel_l2(y, _ref(x1, w1, torch.zeros_like(b), dy)[0]) < 4e-6
+    x1, w1 = _scaled(x, 120, [5]), _scaled(w, -120, [5])
+    y = _run(shape, x1, w1, torch.zeros_like(b), dy)[0]
+    assert rel_l2(y, _ref(x1, w1, torch.zeros_like(b), dy)[0]) < 4e-6
+    m, ki, ns = 129, 300, 200
+    a, f = _scaled(_rand(m, ki), -120, [7]), _scaled(_rand(ki, ns, seed=1).T.contiguous(), 120, [7]).T
+    d = sb.fc_desc(m, ki, ns, sb.SB_F32)
+    out = torch.full((m, ns), 7.0, device="cuda")
+    sb.sb_fc_shard_fwd(d, _dev(a), _dev(f.contiguous()), None, out,
+                       _ws(sb.sb_fc_workspace_bytes(d, sb.SB_FC_FWD)))
+    assert rel_l2(out.cpu(), a.double() @ f.double()) < 4e-6
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 @pytest.mark.parametrize("everywhere", [True, False])
