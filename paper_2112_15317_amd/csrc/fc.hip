@@ -55,11 +55,14 @@ namespace sb {
 // the fp32 MFMA kernels before, 106 like this; the staging waves' loads and
 // vector ALU bound it (dW product 34 us: 25 without the loads, 30 without the
 // splitting, 27 with one MFMA in six).
-constexpr int kGThreads = 512;
+constexpr int kGThreads = 512, kGLocal = 4;
 
-template <int BM_, int BN_, int KO_, int NP_>
+// LOC: bf16 products are summed inside the MFMA over kGLocal steps of 32 k and
+// then added to the accumulators (split ones always are, after every step).
+template <int BM_, int BN_, int KO_, int NP_, bool LOC_>
 struct GemmTile {
   static constexpr int BM = BM_, BN = BN_, KO = KO_, NP = NP_;
+  static constexpr bool LOC = LOC_;
   static constexpr int RB = BM / 32, CB = BN / 32;          // 16 x 16 blocks per wave
   static_assert(BM * KO == 512 && BN * KO == 512, "two pieces of each operand per staging lane");
   // 8-k planes 4 rows apart modulo 16: the planes that neighbouring lanes write
@@ -319,6 +322,21 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
 #pragma unroll
       for (int j = 0; j < T::CB; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
     }
+    constexpr int LI = T::LOC ? T::RB : 1, LJ = T::LOC ? T::CB : 1;
+    f4 loc[LI][LJ];
+#pragma unroll
+    for (int i = 0; i < LI; ++i)
+#pragma unroll
+      for (int j = 0; j < LJ; ++j) loc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    auto add_local = [&]() {
+#pragma unroll
+      for (int i = 0; i < LI; ++i)
+#pragma unroll
+        for (int j = 0; j < LJ; ++j) {
+          acc[i][j] += loc[i][j];
+          loc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
     s8 fa[2][T::RB][T::NP], fb[2][T::NP];
     auto rd_a = [&](const u16* S, int step, int s) {
 #pragma unroll
@@ -348,7 +366,9 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
         __builtin_amdgcn_sched_barrier(0);         // keep those reads ahead of the MFMAs
 #pragma unroll
         for (int i = 0; i < T::RB; ++i) {
-          if constexpr (T::NP == 1) {
+          if constexpr (T::LOC) {
+            loc[i][j] = mfma16x16x32(fa[s][i][0], fb[j & 1][0], loc[i][j]);
+          } else if constexpr (T::NP == 1) {
             acc[i][j] = mfma16x16x32(fa[s][i][0], fb[j & 1][0], acc[i][j]);
           } else {
             f4 c = f4{0.f, 0.f, 0.f, 0.f};
@@ -383,6 +403,7 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
         step(std::integral_constant<int, s0>{}, S, S, 0, 1);
         step(std::integral_constant<int, s0 ^ 1>{}, S, S2, 1, 0);
       }
+      if (T::LOC && (t + 1) % (kGLocal / STEPS) == 0) add_local();
       __syncthreads();
     };
     int t = 0;
@@ -393,6 +414,7 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
     if (t < nk) stage(std::integral_constant<int, 0>{}, t);
 #pragma unroll
     for (int i = 0; i < T::RB; ++i) acc[i][T::CB - 1] += cp[i];
+    if constexpr (T::LOC) add_local();
     if (T::NP == 3 && split_suspect(acc)) *redo = 1;
     // acc[i][j] element v: row wm*BM/2 + 16 i + 4 lq + v, column wn*BN/2 + 16 j + lr.
 #pragma unroll
@@ -459,7 +481,8 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
 
 // out[m, n] = epi(sum_s part[s][m][n]): + bias[n], ReLU, + out (accumulate),
 // rounded to the output type CE.  Four consecutive outputs per thread when
-// N is a multiple of 4 (the splits summed in order for each of them).  The
+// N is a multiple of 4; the splits are summed in order, in fours or
+// eights (16 splits round 4 times at the size of the sum instead of 16).  The
 // blocks past the output add up the splits' column sums csum [splits][N] (db).
 template <class CE>
 __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
@@ -472,14 +495,27 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
     const int n = (int)(blockIdx.x - blocks) * 256 + threadIdx.x;
     if (n >= N) return;
     float v = 0.f;
-    for (int s = 0; s < splits; ++s) v += csum[(size_t)s * N + n];
+    int s = 0;
+    for (; s + 4 <= splits; s += 4)
+      v += (csum[(size_t)s * N + n] + csum[(size_t)(s + 1) * N + n]) +
+           (csum[(size_t)(s + 2) * N + n] + csum[(size_t)(s + 3) * N + n]);
+    for (; s < splits; ++s) v += csum[(size_t)s * N + n];
     db[n] = db_accumulate ? db[n] + v : v;
     return;
   }
   const size_t i4 = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i4 >= stride) return;
   if (N % 4 == 0) {
-    const f4 v = split_sum4(part, splits, stride, i4);
+    f4 v = f4{0.f, 0.f, 0.f, 0.f};
+    int s = 0;
+    for (; s + 4 <= splits; s += 4) {              // four loads in flight
+      f4 p[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        p[q] = *reinterpret_cast<const f4*>(part + (size_t)(s + q) * stride + i4);
+      v += (p[0] + p[1]) + (p[2] + p[3]);
+    }
+    for (; s < splits; ++s) v += *reinterpret_cast<const f4*>(part + (size_t)s * stride + i4);
     const int m = (int)(i4 / N), n = (int)(i4 - (size_t)m * N);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -502,8 +538,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
       float p[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) p[q] = part[(size_t)(s + q) * stride + i];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) x += p[q];
+      x += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
     }
     for (; s < splits; ++s) x += part[(size_t)s * stride + i];
     if (bias) x += bias[n];
@@ -567,8 +602,18 @@ static void gemm_launch_t(const GemmPlan& p, const GemmArgs& g, hipStream_t st) 
 template <bool AK, bool BK, bool VEC, class E, class CE, bool AMK, bool BMK>
 static void gemm_launch_m(const GemmPlan& p, const GemmArgs& g, hipStream_t st) {
   constexpr int NP = sizeof(E) == 2 ? 1 : 3;
-  if (p.bm == 128) gemm_launch_t<GemmTile<128, 128, 4, NP>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
-  else gemm_launch_t<GemmTile<64, 64, 8, NP>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+  constexpr bool B16 = NP == 1;
+  // The MFMA drops low bits always in one direction, so long bf16 sums are
+  // taken out of it every 128 k (dW of 1024 rows against 64 bits 1.4e-7 with all
+  // of them inside, 1.0e-7 like this, 1.1e-7 on the fp32 MFMA).  Shorter ones
+  // stay inside on the large tile: 119 registers instead of 183 leave room
+  // for two blocks a CU (dW of 84 rows, 6787 x 692: 18.6 us instead of 21.8).
+  if (p.bm == 64)
+    gemm_launch_t<GemmTile<64, 64, 8, NP, B16>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+  else if (B16 && p.kps > 32 * kGLocal)
+    gemm_launch_t<GemmTile<128, 128, 4, NP, B16>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+  else
+    gemm_launch_t<GemmTile<128, 128, 4, NP, false>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
 }
 
 // The masks are template arguments, so that no load or store of the

@@ -217,6 +217,26 @@ def test_fc_against_64_bits(m, ki, ns):
     assert bad.nonzero().flatten().tolist() == [ki // 2] and not torch.isfinite(dw[ki // 2]).any()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,ki,ns", [(1024, 1024, 1024), (1024, 128, 64), (1000, 300, 200)])
+def test_bf16_fc_weight_gradient_does_not_drift(m, ki, ns):
+    # Positive terms, exact products: a split's sum is rounded at its own size
+    # once per 128 rows, eight times here, and the splits' sums twice: as random
+    # roundings of a sum that grows evenly sqrt(10 / 3) * 2^-25 = 5.4e-8.  The
+    # bf16 MFMA drops low bits always downwards within the 128 rows: 4 steps of
+    # half a unit at an eighth of the sum's size, 2^-24 / 4 = 1.5e-8.
+    print_case("bf16 fc dw", m=m, ki=ki, ns=ns)
+    x, dy = (_rand(*s, seed=i).abs().bfloat16() for i, s in enumerate(((m, ki), (m, ns))))
+    w = _rand(ki, ns, seed=3).bfloat16()
+    d = sb.fc_desc(m, ki, ns, sb.SB_BF16)
+    dw = torch.full((ki, ns), 7.0, device="cuda")
+    sb.sb_fc_shard_bwd(d, x.cuda(), w.cuda(), dy.cuda(), None, None, dw, None, False,
+                       _ws(sb.sb_fc_workspace_bytes(d, sb.SB_FC_BWD)))
+    err = rel_l2(dw.cpu(), x.double().T @ dy.double())
+    print("error", err)
+    assert err < 7e-8
+
+
 # Scales of x, w and dy: small operands that meet large ones, so that their
 # products are ordinary numbers (sums of 1e4 products of 2^108 stay below 2^117);
 # 2^-140 against 1, whose products are subnormal.
