@@ -24,14 +24,15 @@
 namespace sb {
 
 // ---------------------------------------------------------------------------
-// GEMM core.  C = epi(A * B) with A [M x K], B [K x N].  A block of 512 threads
-// has a CU to itself: four waves stage, four multiply (2 x 2, each BM/2 x BN/2
+// GEMM core.  C = epi(A * B) with A [M x K], B [K x N].  Blocks of 512 threads,
+// one or two a CU: four waves stage, four multiply (2 x 2, each BM/2 x BN/2
 // as 16 x 16 blocks of the 16x16x32 MFMA).
 //
 // A stage is 8*KO of the reduction, kept in LDS as [part][k / 8][row][k % 8] for
 // both operands whatever their layout in memory, so an MFMA operand is one
 // 16-byte read per lane.  A staging lane makes two 16-byte pieces (8 k of a row)
-// of each operand per stage:
+// of each operand per stage, or two of one operand (64 x 64 tiles of 32 k: two
+// waves stage A, two B):
 //   * contiguous along k ("K-contiguous"): two pieces of 8 consecutive elements;
 //   * contiguous along its rows: 8 k of two adjacent rows, transposed in
 //     registers.
@@ -51,8 +52,12 @@ namespace sb {
 // colsum (the FC bias gradient): the staging waves of the first row tile's
 // blocks add up the B values they stage.
 //
+// A tile leaves through LDS; a thread's pieces share their columns, so the bias
+// is loaded once and several pieces are under way at a time (one by one, each
+// waiting for its bias, they cost 1024 x 2048 outputs of 128 k 3 us of 16.6).
+//
 // Measured (512 x 4096 x 1024 fp32 shard, forward and backward): 132 us with
-// the fp32 MFMA kernels before, 106 like this; the staging waves' loads and
+// the fp32 MFMA kernels before, 104 like this; the staging waves' loads and
 // vector ALU bound it (dW product 34 us: 25 without the loads, 30 without the
 // splitting, 27 with one MFMA in six).
 constexpr int kGThreads = 512, kGLocal = 4;
@@ -64,7 +69,9 @@ struct GemmTile {
   static constexpr int BM = BM_, BN = BN_, KO = KO_, NP = NP_;
   static constexpr bool LOC = LOC_;
   static constexpr int RB = BM / 32, CB = BN / 32;          // 16 x 16 blocks per wave
-  static_assert(BM * KO == 512 && BN * KO == 512, "two pieces of each operand per staging lane");
+  static_assert(BM == BN && (BM * KO == 512 || BM * KO == 256), "two pieces per staging lane");
+  // Staging lanes of an operand: all of them, or two waves for A and two for B.
+  static constexpr int LANES = BM * KO / 2;
   // 8-k planes 4 rows apart modulo 16: the planes that neighbouring lanes write
   // start in different banks.
   static constexpr int APL = BM + 4, BPL = BN + 4;
@@ -103,7 +110,7 @@ struct GStage {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       if (KC) {                                    // piece u: k octet fastest
-        const int u = ptid + 256 * i;
+        const int u = ptid + ROWS * KO / 2 * i;
         oct[i] = u % KO;
         row[i] = r0 + u / KO;
       } else {                                     // rows 2p, 2p + 1
@@ -235,7 +242,7 @@ __device__ __forceinline__ void gemm_tile_f32(const GemmArgs& g, float* O, int m
 }
 
 template <class T, bool A_KC, bool B_KC, bool VEC, class E, class CE, bool AMK, bool BMK>
-__global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
+__global__ __launch_bounds__(kGThreads, T::LANES == 256 ? 2 : 4) void gemm_split(GemmArgs g) {
   extern __shared__ u16 ldsu[];
   float* O = reinterpret_cast<float*>(ldsu);
   constexpr int KS = T::KO * 8;                    // k per stage
@@ -261,54 +268,75 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
     const rsrc_t rb = make_rsrc(g.b, (uint32_t)(b_elems * sizeof(E)));
     const rsrc_t ram = make_rsrc(AMK ? g.amask : g.a, (uint32_t)(a_elems * sizeof(E)));
     const rsrc_t rbm = make_rsrc(BMK ? g.bmask : g.b, (uint32_t)(b_elems * sizeof(E)));
-    GStage<T::BM, T::KO, T::APL, T::APART, T::NP, A_KC, VEC, E, AMK> sa;
-    GStage<T::BN, T::KO, T::BPL, T::BPART, T::NP, B_KC, VEC, E, BMK> sb_;
-    sa.init(g.lda, g.M, m0, ptid);
-    sb_.init(g.ldb, g.N, n0, ptid);
+    using StageA = GStage<T::BM, T::KO, T::APL, T::APART, T::NP, A_KC, VEC, E, AMK>;
+    using StageB = GStage<T::BN, T::KO, T::BPL, T::BPART, T::NP, B_KC, VEC, E, BMK>;
     uint32_t lost = 0;
     float cs[2] = {0.f, 0.f};                      // column sums of this lane's two rows of B
-    auto add_cols = [&](const auto& q) {
+    auto load_a = [&](StageA& q, int t) { q.load(ra, ram, kb + t * KS, ke); };
+    auto load_b = [&](StageB& q, int t) { q.load(rb, rbm, kb + t * KS, ke); };
+    auto store_a = [&](StageA& q, int t) { q.store(ldsu + t % 3 * T::STAGE, m0, lost); };
+    auto store_b = [&](StageB& q, int t) {
+      q.store(ldsu + t % 3 * T::STAGE + T::LDS_A, n0, lost);
+      if (!B_KC && do_colsum) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        cs[i] += ((q.v[i][0] + q.v[i][1]) + (q.v[i][2] + q.v[i][3])) +
-                 ((q.v[i][4] + q.v[i][5]) + (q.v[i][6] + q.v[i][7]));
+        for (int i = 0; i < 2; ++i)
+          cs[i] += ((q.v[i][0] + q.v[i][1]) + (q.v[i][2] + q.v[i][3])) +
+                   ((q.v[i][4] + q.v[i][5]) + (q.v[i][6] + q.v[i][7]));
+      }
     };
-    auto load = [&](int t) {                       // a stage past the end loads zeros
-      sa.load(ra, ram, kb + t * KS, ke);
-      sb_.load(rb, rbm, kb + t * KS, ke);
-    };
-    auto store = [&](int t) {
-      u16* S = ldsu + t % 3 * T::STAGE;
-      sa.store(S, m0, lost);
-      sb_.store(S + T::LDS_A, n0, lost);
-      if (!B_KC && do_colsum) add_cols(sb_);
-    };
-    if (nk > 1) {                                  // both loads in flight at once
-      GStage<T::BM, T::KO, T::APL, T::APART, T::NP, A_KC, VEC, E, AMK> sa0 = sa;
-      GStage<T::BN, T::KO, T::BPL, T::BPART, T::NP, B_KC, VEC, E, BMK> sb0 = sb_;
-      sa0.load(ra, ram, kb, ke);
-      sb0.load(rb, rbm, kb, ke);
-      load(1);
-      sa0.store(ldsu, m0, lost);
-      sb0.store(ldsu + T::LDS_A, n0, lost);
-      if (!B_KC && do_colsum) add_cols(sb0);
-      store(1);
-    } else {
-      load(0);
-      store(0);
-    }
-    if (nk > 2) load(2);
-    __syncthreads();
-    for (int t = 0; t < nk; ++t) {
-      if (t + 2 < nk) store(t + 2);
-      if (t + 3 < nk) load(t + 3);
+    // load0 / store0: the first stage through registers of its own, so that the
+    // first two loads are in flight at once.  A stage past the end loads zeros.
+    auto pipeline = [&](auto&& load0, auto&& store0, auto&& load, auto&& store) {
+      if (nk > 1) {
+        load0(0);
+        load(1);
+        store0(0);
+        store(1);
+      } else {
+        load(0);
+        store(0);
+      }
+      if (nk > 2) load(2);
       __syncthreads();
+      for (int t = 0; t < nk; ++t) {
+        if (t + 2 < nk) store(t + 2);
+        if (t + 3 < nk) load(t + 3);
+        __syncthreads();
+      }
+    };
+    auto put_sums = [&](const StageB& q) {         // [octet][row] after the output tile
+      if (!B_KC && do_colsum) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) O[T::BM * T::EP + q.oct[i] * T::BN + q.row[i] - n0] = cs[i];
+      }
+    };
+    if constexpr (T::LANES == 256) {
+      StageA a;
+      StageB b;
+      a.init(g.lda, g.M, m0, ptid);
+      b.init(g.ldb, g.N, n0, ptid);
+      StageA a0 = a;
+      StageB b0 = b;
+      pipeline([&](int t) { load_a(a0, t); load_b(b0, t); },
+               [&](int t) { store_a(a0, t); store_b(b0, t); },
+               [&](int t) { load_a(a, t); load_b(b, t); },
+               [&](int t) { store_a(a, t); store_b(b, t); });
+      put_sums(b);
+    } else if (wave < 6) {
+      StageA a;
+      a.init(g.lda, g.M, m0, ptid);
+      StageA a0 = a;
+      pipeline([&](int t) { load_a(a0, t); }, [&](int t) { store_a(a0, t); },
+               [&](int t) { load_a(a, t); }, [&](int t) { store_a(a, t); });
+    } else {
+      StageB b;
+      b.init(g.ldb, g.N, n0, ptid - T::LANES);
+      StageB b0 = b;
+      pipeline([&](int t) { load_b(b0, t); }, [&](int t) { store_b(b0, t); },
+               [&](int t) { load_b(b, t); }, [&](int t) { store_b(b, t); });
+      put_sums(b);
     }
     if (T::NP == 3 && (lost & 0xffffu)) *redo = 1;
-    if (!B_KC && do_colsum) {                      // [octet][row] after the output tile
-#pragma unroll
-      for (int i = 0; i < 2; ++i) O[T::BM * T::EP + sb_.oct[i] * T::BN + sb_.row[i] - n0] = cs[i];
-    }
   } else {
     // ---- multiplying waves ----
     const int lr = lane & 15, lq = lane >> 4;
@@ -447,17 +475,26 @@ __global__ __launch_bounds__(kGThreads, 2) void gemm_split(GemmArgs g) {
   const bool vec4 = g.N % 4 == 0 && g.ldc % 4 == 0 &&
                     ((uintptr_t)(partial ? (void*)part : g.c) &
                      (partial ? 15 : 4 * sizeof(CE) - 1)) == 0;
-#pragma unroll 1
-  for (int q = tid; q < T::BM * T::BN / 4; q += kGThreads) {
-    const int r = q / (T::BN / 4), c = q % (T::BN / 4) * 4;
-    const int m = m0 + r, n = n0 + c;
-    if (m >= g.M || n >= g.N) continue;
+  // A thread's quads share their columns.
+  static_assert(kGThreads % (T::BN / 4) == 0, "one column quad per thread");
+  const int c = tid % (T::BN / 4) * 4, n = n0 + c;
+  if (n >= g.N) return;
+  f4 bias = f4{0.f, 0.f, 0.f, 0.f};
+  if (!partial && g.bias) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < g.N) bias[e] = g.bias[n + e];
+  }
+#pragma unroll 4
+  for (int r = tid / (T::BN / 4); r < T::BM; r += kGThreads / (T::BN / 4)) {
+    const int m = m0 + r;
+    if (m >= g.M) break;
     f4 v = *reinterpret_cast<const f4*>(O + r * T::EP + c);
     const size_t o = (size_t)m * g.ldc + n;
     if (!partial) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (g.bias && n + e < g.N) v[e] += g.bias[n + e];
+        v[e] += bias[e];
         if (g.relu && !(v[e] > 0.f)) v[e] = 0.f;
       }
     }
@@ -550,28 +587,55 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
 }
 
 // Tile shape and split of one GEMM: the least estimated time over 128x128 and
-// 64x64 block tiles and 1 to 32 ranges of k.  A block per CU takes about 4 us
-// for its first stages and its output; per 32 k a 128x128 tile takes 0.9 us and
-// a 64x64 tile, a fourth of the products on the same staging, 0.4 (bf16: 0.3 and
-// 0.2, the staging); partials cost their traffic and a launch.
-struct GemmPlan { int bm, mt, nt, splits, kps; size_t ws_bytes; };
+// 64x64 block tiles and 1 to 32 ranges of k.
+//   * A 64x64 tile stages 32 k at a time in fp32, so that two blocks share a CU
+//     and one's first loads and output run beside the other's products: 1024 x
+//     2048 outputs of 128 k 13.1 -> 9.8 us, 4096 x 512 of 128 k 13.2 -> 10.4.
+//     Two K-contiguous operands of element loads stay with 64 k and one block
+//     (479 x 741 outputs of 1859 k: 56.9 us, with 32 k 61.3), bf16 too, whose
+//     blocks are small enough (512 x 4096 of 1024 k: 22.4 us, with 32 k 28.3).
+//   * Costs in us: `block` for a block's first stages and output, `k32` for 32
+//     k, `elems` times as much (X W, dY W^T, X^T dY) where rows allow element
+//     loads alone; blocks that share a CU take `alone` of the loop's time where
+//     one has it to itself; split partials a launch, `each`, and their traffic,
+//     `odd` times as much where outputs are added one by one.
+// Fitted to 15000 timings of the three products of 104 shards under forced plans
+// in both types: the plan taken is 0.8 % slower than the best one on average, 19 %
+// at most, where one block a CU at the same cost for all operands lost 4 % (fp32)
+// and 12 % (bf16), up to 2.1 times.
+struct GemmPlan { int bm, ko, mt, nt, splits, kps; size_t ws_bytes; };
+struct GemmCost { double block[2], k32[2], elems[2][3], alone, split, each, tb_s, odd; };
+static const GemmCost kGCost[2] = {
+    {{3.44, 1.35}, {1.74, 1.08}, {{0.63, 1.28, 1.61}, {0.88, 1.17, 1.61}},       // fp32
+     0.68, 2.16, 0.11, 5.61, 1.58},
+    {{3.69, 1.30}, {0.95, 0.63}, {{1.28, 1.47, 2.17}, {1.37, 1.65, 2.91}},       // bf16
+     0.72, 2.50, 0.13, 5.24, 3.5}};
 
-static GemmPlan gemm_plan(int M, int N, int K, int esize) {
+// ak, bk: A, B contiguous along k; aligned: their rows allow vector staging.
+static GemmPlan gemm_plan(int M, int N, int K, int esize, bool ak, bool bk, bool aligned) {
+  const bool b16 = esize == 2;
+  const GemmCost& c = kGCost[b16];
+  const double traffic = (double)M * N * 4e-6 / c.tb_s * (N % 4 ? c.odd : 1.0);
   GemmPlan best{};
   double best_t = 0;
-  for (int bm : {128, 64}) {
-    const int ks = bm == 128 ? 32 : 64;                     // k per stage
-    const double t32 = esize == 2 ? (bm == 128 ? 0.3 : 0.2) : (bm == 128 ? 0.9 : 0.4);
+  for (int i = 0; i < 2; ++i) {
+    const int bm = i == 0 ? 128 : 64, ko = i == 1 && (b16 || (ak && bk && !aligned)) ? 8 : 4;
+    const int ks = ko * 8;                                   // k per stage
+    const double elems = aligned ? 1.0 : c.elems[i][ak ? (bk ? 1 : 0) : 2];
     const int mt = cdiv(M, bm), nt = cdiv(N, bm), ktiles = cdiv(K, ks);
     for (int s = 1; s <= 32 && s <= ktiles; ++s) {
       const int tps = cdiv(ktiles, s);
       if (cdiv(ktiles, tps) != s) continue;
-      const double est = (double)cdiv((int)std::min<long>((long)mt * nt * s, 1l << 30), 256) *
-                             (4.0 + t32 * tps * ks / 32) +
-                         (s > 1 ? 2.0 + (double)M * N * 4e-6 * (2 * s + 1) / 4.0 : 0.0);
+      const bool two = b16 ? bm == 64 || tps * ks <= 32 * kGLocal : bm == 64 && ko == 4;
+      const long round = two ? 512 : 256, blocks = (long)mt * nt * s, rest = blocks % round;
+      const double loop = c.k32[i] * elems * tps * ks / 32;
+      const double all = c.block[i] + loop, alone = c.block[i] + (two ? c.alone : 1.0) * loop;
+      const double est =
+          (double)(blocks / round) * all + (rest == 0 ? 0.0 : rest <= 256 ? alone : all) +
+          (s > 1 ? c.split + c.each * s + traffic * (2 * s + 1) : 0.0);
       if (best_t == 0 || est < best_t) {
         best_t = est;
-        best = GemmPlan{bm, mt, nt, s, tps * ks, 0};
+        best = GemmPlan{bm, ko, mt, nt, s, tps * ks, 0};
       }
     }
   }
@@ -582,10 +646,21 @@ static GemmPlan gemm_plan(int M, int N, int K, int esize) {
 
 // Vector staging: K-contiguous operands in groups of 4 elements along k,
 // row-contiguous ones in pairs of rows.
+static bool vec_dims(int ld, int contiguous_extent, bool kc) {
+  const int n = kc ? 4 : 2;
+  return ld % n == 0 && contiguous_extent % n == 0;
+}
 template <class E>
 static bool vec_ok(const void* p, int ld, int contiguous_extent, bool kc) {
-  const int n = kc ? 4 : 2;
-  return ((uintptr_t)p & (n * sizeof(E) - 1)) == 0 && ld % n == 0 && contiguous_extent % n == 0;
+  return ((uintptr_t)p & ((kc ? 4 : 2) * sizeof(E) - 1)) == 0 &&
+         vec_dims(ld, contiguous_extent, kc);
+}
+
+// The plan of a product with operands of these layouts; it does not depend on
+// the tensors' addresses, which the workspace query does not know.
+static GemmPlan product_plan(int M, int N, int K, int lda, bool ak, int ldb, bool bk, int esize) {
+  return gemm_plan(M, N, K, esize, ak, bk,
+                   vec_dims(lda, ak ? K : M, ak) && vec_dims(ldb, bk ? K : N, bk));
 }
 
 template <class T, bool AK, bool BK, bool VEC, class E, class CE, bool AMK, bool BMK>
@@ -605,15 +680,25 @@ static void gemm_launch_m(const GemmPlan& p, const GemmArgs& g, hipStream_t st) 
   constexpr bool B16 = NP == 1;
   // The MFMA drops low bits always in one direction, so long bf16 sums are
   // taken out of it every 128 k (dW of 1024 rows against 64 bits 1.4e-7 with all
-  // of them inside, 1.0e-7 like this, 1.1e-7 on the fp32 MFMA).  Shorter ones
+  // of them inside, 7e-8 like this, 1.1e-7 on the fp32 MFMA).  Shorter ones
   // stay inside on the large tile: 119 registers instead of 183 leave room
   // for two blocks a CU (dW of 84 rows, 6787 x 692: 18.6 us instead of 21.8).
-  if (p.bm == 64)
+  if (p.bm == 128) {
+    if (B16 && p.kps > 32 * kGLocal)
+      gemm_launch_t<GemmTile<128, 128, 4, NP, B16>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+    else
+      gemm_launch_t<GemmTile<128, 128, 4, NP, false>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+    return;
+  }
+  constexpr bool WIDE = B16 || (AK && BK && !VEC);   // where the plan may stage 64 k at a time
+  if constexpr (!B16) {
+    if (!WIDE || p.ko == 4) {
+      gemm_launch_t<GemmTile<64, 64, 4, NP, false>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
+      return;
+    }
+  }
+  if constexpr (WIDE)
     gemm_launch_t<GemmTile<64, 64, 8, NP, B16>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
-  else if (B16 && p.kps > 32 * kGLocal)
-    gemm_launch_t<GemmTile<128, 128, 4, NP, B16>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
-  else
-    gemm_launch_t<GemmTile<128, 128, 4, NP, false>, AK, BK, VEC, E, CE, AMK, BMK>(p, g, st);
 }
 
 // The masks are template arguments, so that no load or store of the
@@ -639,7 +724,7 @@ template <bool AK, bool BK, class E, class CE>
 static sb_status gemm_run(GemmArgs g, float* ws, size_t ws_bytes, hipStream_t st) {
   // Masks exist only where gemm_launch instantiates them.
   if ((g.amask && !(AK && BK)) || (g.bmask && (AK || BK))) return SB_ERR_UNSUPPORTED;
-  GemmPlan p = gemm_plan(g.M, g.N, g.K, (int)sizeof(E));
+  const GemmPlan p = product_plan(g.M, g.N, g.K, g.lda, AK, g.ldb, BK, (int)sizeof(E));
   if (p.ws_bytes > 0 && (!ws || ws_bytes < p.ws_bytes)) return SB_ERR_WORKSPACE;
   // Buffer ranges cover whole operands.
   const int64_t a_elems = AK ? (int64_t)(g.M - 1) * g.lda + g.K : (int64_t)(g.K - 1) * g.lda + g.M;
@@ -675,10 +760,6 @@ static sb_status gemm_run(GemmArgs g, float* ws, size_t ws_bytes, hipStream_t st
   return SB_OK;
 }
 
-static size_t gemm_ws(int M, int N, int K, int esize) {
-  return gemm_plan(M, N, K, esize).ws_bytes;
-}
-
 }  // namespace sb
 
 using namespace sb;
@@ -695,9 +776,11 @@ static sb_status fc_check(const sb_fc_desc* d) {
 extern "C" size_t sb_fc_workspace_bytes(const sb_fc_desc* d, int pass) {
   if (fc_check(d) != SB_OK) return (size_t)-1;
   const int es = d->dtype == SB_BF16 ? 2 : 4;
-  if (pass == SB_FC_FWD) return gemm_ws(d->m, d->n_shard, d->k_in, es);
+  const int m = d->m, kin = d->k_in, ns = d->n_shard;
+  if (pass == SB_FC_FWD) return product_plan(m, ns, kin, d->ldx, true, ns, false, es).ws_bytes;
   if (pass == SB_FC_BWD)   // dX partial, then dW: the two share the workspace
-    return std::max(gemm_ws(d->m, d->k_in, d->n_shard, es), gemm_ws(d->k_in, d->n_shard, d->m, es));
+    return std::max(product_plan(m, kin, ns, d->ldy, true, ns, true, es).ws_bytes,
+                    product_plan(kin, ns, m, d->ldx, false, d->ldy, false, es).ws_bytes);
   return (size_t)-1;
 }
 

@@ -188,7 +188,9 @@ def test_pooled_forward_is_the_forward_pooled(shape):
 @pytest.mark.gpu
 @pytest.mark.parametrize("m,ki,ns", [(1, 33, 1), (63, 65, 127), (64, 64, 64), (65, 31, 130),
                                      (128, 256, 128), (129, 1000, 66), (512, 512, 1024),
-                                     (1000, 130, 40), (32, 4100, 257)])
+                                     (1000, 130, 40), (32, 4100, 257), (1024, 128, 2048),
+                                     (1023, 129, 2047), (128, 4096, 512), (479, 741, 1859),
+                                     (65, 607, 314), (96, 300, 1500), (250, 2729, 599)])
 def test_fc_against_64_bits(m, ki, ns):
     print_case("split fc", m=m, ki=ki, ns=ns)
     x, w, b = _rand(m, ki, seed=1), _rand(ki, ns, seed=2, scale=ki ** -0.5), _rand(ns, seed=3)
@@ -215,6 +217,47 @@ def test_fc_against_64_bits(m, ki, ns):
     assert torch.isinf(y).any(1).nonzero().flatten().tolist() == [m // 2]
     bad = ~torch.isfinite(dw).all(1)
     assert bad.nonzero().flatten().tolist() == [ki // 2] and not torch.isfinite(dw[ki // 2]).any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,ki,ns,forward", [(1024, 128, 2048, True), (1024, 64, 2048, True),
+                                             (128, 4096, 512, False), (224, 5536, 192, False)])
+def test_short_reductions_fill_the_chip(m, ki, ns, forward):
+    # Many outputs of 64 to 224 terms beside the 512 x 4096 x 1024 forward (41
+    # us) of the same process: 0.20 to 0.29 of it (8 to 12 us), the fp32 MFMA's 9
+    # to 15 us likewise.  Output loops that wait for their bias piece by piece
+    # and one block a CU take 0.36 to 0.45 (15 to 19 us).
+    print_case("fc short reduction", m=m, ki=ki, ns=ns, forward=forward)
+
+    def call(m, ki, ns, forward):
+        d = sb.fc_desc(m, ki, ns, sb.SB_F32)
+        ws = _ws(max(sb.sb_fc_workspace_bytes(d, p) for p in (sb.SB_FC_FWD, sb.SB_FC_BWD)))
+        x, w, b, dy = (_dev(_rand(*s)) for s in ((m, ki), (ki, ns), (ns,), (m, ns)))
+        y, dw, db = (torch.empty_like(t) for t in (dy, w, b))
+        if forward:
+            return lambda: sb.sb_fc_shard_fwd(d, x, w, b, y, ws)
+        return lambda: sb.sb_fc_shard_bwd(d, x, w, dy, None, None, dw, db, False, ws)
+
+    def us(f):
+        f()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for _ in range(20):
+                f()
+        best = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            g.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best.append(a.elapsed_time(b) * 50)
+        return min(best)
+
+    t, whole = us(call(m, ki, ns, forward)), us(call(512, 4096, 1024, True))
+    print("us", t, whole)
+    assert t < 0.325 * whole, (t, whole)
 
 
 @pytest.mark.gpu
