@@ -573,7 +573,8 @@ def kernel_name(key, call_args, dtype):
     if kind == "wgrad_many":       # one launch of the batched kernel for the group
         wl = call_args[0]
         name = sb.sb_conv3x3_plan_string(wl.descs[0], sb.SB_PASS_BWD_WEIGHT).split(" grid=")[0]
-        return name.replace("conv3x3_wgrad_split<", "conv3x3_wgrad_split_many<") + \
+        return name.replace("conv3x3_wgrad_split<", "conv3x3_wgrad_split_many<").replace(
+            "conv3x3_wgrad_f32<", "conv3x3_wgrad_f32_many<") + \
             " grid=%dx1x2" % wl.count
     if kind.startswith("fc_"):
         d = call_args[0]

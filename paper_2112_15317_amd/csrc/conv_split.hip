@@ -440,6 +440,7 @@ __global__ __launch_bounds__(256) void filter_pack_split(const float* __restrict
 struct SPlan {
   int tile, imgs, tiles_w, tiles_h, ptiles, co_tiles, nchunks, cps, splits;
   size_t pack_bytes, part_off, ws_bytes;
+  double us;                              // estimated time
 };
 
 // Tile table: spatial tile (rows, columns, images), waves along channels,
@@ -488,11 +489,11 @@ static SPlan split_plan(int N, int Cin, int H, int W, int Cout) {
       p.cps = cdiv(rounds, s) * t.wk;
       p.splits = cdiv(nchunks, p.cps);
       if (p.splits != s) continue;
-      const long blocks = (long)p.ptiles * p.co_tiles * s;
+      const long blocks = std::min<long>((long)p.ptiles * p.co_tiles * s, 1l << 30);
       const double out_mb = (double)N * Cout * H * W * 4e-6;
       const double est = cdiv((int)blocks, 256) * (5.0 + 7.2 * cdiv(std::min(p.cps, nchunks), t.wk)) +
                          (s > 1 ? 3.0 + out_mb * (s + 1) / 4.0 : 0.0);
-      if (best_t == 0 || est < best_t) { best = p; best_t = est; }
+      if (best_t == 0 || est < best_t) { best = p; best_t = best.us = est; }
     }
   }
   best.pack_bytes = (size_t)cdiv(Cout, 16) * nchunks * kSplitSlice * sizeof(u16);
@@ -548,18 +549,40 @@ static void split_dispatch(const SPlan& p, const ConvArgs& a, hipStream_t st) {
 
 namespace sbh {
 
+// Estimated time in us of the fp32-MFMA kernels of conv_igemm.hip: rounds of 512
+// blocks of 64 channels x 128 pixels (their tiles: 4x32, 8x16, 2 images of 8x8,
+// 8 of 4x4), split over chunks of 8 channels where they are fewer.
+static double fp32_mfma_us(int N, int Cin, int H, int W, int Cout) {
+  using sb::cdiv;
+  long tiles;
+  if (W >= 32) tiles = (long)N * cdiv(W, 32) * cdiv(H, 4);
+  else if (W >= 16) tiles = (long)N * cdiv(W, 16) * cdiv(H, 8);
+  else if (W >= 8) tiles = (long)cdiv(N, 2) * cdiv(W, 8) * cdiv(H, 8);
+  else if (W == 4 && H == 4) tiles = 2 * cdiv(N, 16);
+  else tiles = (long)cdiv(N, 8) * cdiv(W, 4) * cdiv(H, 4);
+  const long blocks = tiles * cdiv(Cout, 64);
+  const int nchunks = cdiv(Cin, 8);
+  int splits = 1;
+  if (blocks < 512)
+    splits = (int)std::min<long>(std::min(8, std::max(1, nchunks / 2)), (512 + blocks - 1) / blocks);
+  const int cps = cdiv(nchunks, splits);
+  splits = cdiv(nchunks, cps);
+  const long all = blocks * splits;
+  return 1.73 + (double)((all + 511) / 512) * (0.54 + 2.63 * cps) + 3.83 * all / 512 * cps +
+         (splits > 1 ? 2.25 + 0.83e-6 * N * Cout * H * W * (splits + 1) : 0.0);
+}
+
 // Whether an fp32 pass runs here; the fp32-MFMA kernels of conv_igemm.hip take
 // the others.  Never: images narrower than 4 (2x2 kernels skip the 56 % of the
 // products that are padding), 16 input channels or fewer (a chunk is 32), wide
 // images of 16 output channels or fewer (a tile is 64), sizes whose offsets
-// pass 2^31 bytes.  Otherwise by work, as
-// a block needs about 12 us for a tile of one chunk and the chip 256 of them:
-// with v = pixels x Cin x Cout, from 4e7 on, or from 1.2e7 on where at least
-// 6144 pixels make enough tiles.  Forward and data gradient in us, on the fp32
-// MFMA and here: 16x16 128 -> 128, 8 images (3.4e7, 2048 pixels) 44, 50; 16x16
-// 64 -> 48, 20 images (1.6e7, 5120 pixels) 38, 42; 4x4 512 -> 512, 16 images
-// (6.7e7) 85, 64; 14x14 50 -> 60, 40 images (2.4e7, 7840 pixels) 58, 48; 10x10
-// 20 -> 64, 100 images (1.3e7, 10000 pixels) 65, 45.
+// pass 2^31 bytes.  Otherwise where the estimated time is the smaller one; a
+// pass of a single chunk has no loop to hide its first loads in (1.3 us).
+// Fitted to both kernels' times of 597 passes: the one taken is 0.5 % slower than
+// the faster one on average, and slower than the fp32 MFMA in 8, by 14 % at most
+// (a line by work and pixels alone: 5 %, 30, 33 %).  Forward and data gradient
+// in us, fp32 MFMA and here: 16x16 128 -> 128, 8 images 44, 50; 20x20 32 -> 24, 74
+// images 23, 31; 14x14 32 -> 256, 64 images 40, 29; 4x4 512 -> 512, 16 images 85, 64.
 bool conv_split_takes(int N, int Cin, int H, int W, int Cout) {
   if (W < 4 || Cin <= 16 || (W >= 32 && Cout <= 16)) return false;
   // 32-bit offsets: the filters of a wave's four channel blocks, and an image
@@ -568,8 +591,8 @@ bool conv_split_takes(int N, int Cin, int H, int W, int Cout) {
   if (4 * nchunks * sb::kSplitSlice * (int64_t)sizeof(sb::u16) >= (1ll << 31) ||
       (nchunks * 32 + 8) * H * W * 4 >= (1ll << 31))
     return false;
-  const double px = (double)N * H * W, v = px * Cin * Cout;
-  return v >= 4e7 || (W >= 8 && px >= 6144 && v >= 1.2e7);
+  return fp32_mfma_us(N, Cin, H, W, Cout) >
+         1.2 * sb::split_plan(N, Cin, H, W, Cout).us + (nchunks == 1 ? 1.3 : 0.0);
 }
 
 size_t conv_split_ws(int N, int Cin, int H, int W, int Cout, bool prepacked) {

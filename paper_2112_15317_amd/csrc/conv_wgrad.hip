@@ -11,9 +11,6 @@
 // An MFMA against a column of ones in those blocks alone would make them
 // the slowest of the grid.  Three kernels:
 //
-// Most fp32 layers run in conv_wgrad_split.hip instead; small fp32 calls, 2x2
-// images, fewer than 8 input channels and bf16 tensors run here.
-//
 // conv3x3_wgrad_f32 (any shape).  A block owns 64 k and walks a contiguous
 // range of 64-pixel tiles (IMGS images x TH rows x TW cols).  Per pixel tile
 // it stages in LDS dy (64 k x 64 pixels, stored [pixel][k] so an operand
@@ -306,9 +303,29 @@ __device__ __forceinline__ int wg_hoff(int p) {
   return img * T::HH * T::HW + yy * T::HW + xx;
 }
 
-template <class T, class E>
-__global__ __launch_bounds__(256, 2) void conv3x3_wgrad_f32(WgArgs a) {
-  const WgBlock blk = wg_block();
+// Whether the MFMA of 4-pixel step st at tap t only multiplies zero padding
+// when a tile is one whole image (H = TH, W = TW): the step's pixels share a
+// row, and a tap in the top (bottom) filter row reads the padding row above
+// (below) the image for the image's first (last) row.  Known at compile time
+// after unrolling, so those MFMAs are never issued.
+template <class T, bool WHOLE>
+__device__ constexpr bool wg_pad_step(int st, int t) {
+  if (!WHOLE) return false;
+  const int yy = (st * 4) % (T::TH * T::TW) / T::TW;
+  return (t / 3 == 0 && yy == 0) || (t / 3 == 2 && yy == T::TH - 1);
+}
+
+// ROWS: every tile spans the image's full width (IMGS = 1, W = TW), so a
+// staged element's offset within its image is a per-thread constant plus the
+// tile's first row, and only its row can leave the image: the constants are
+// worked out once per thread, and per tile an element costs an add and a row
+// test.  WHOLE (with ROWS): every tile is a whole image (H = TH as well), and
+// the steps whose taps read only padding are skipped (wg_pad_step).
+// The block's work for block (x, z) of the layer `a`; the kernels below
+// pick the layer and the block.
+template <class T, class E, bool ROWS, bool WHOLE>
+__device__ __forceinline__ void wgrad_f32_block(const WgArgs& a, const WgBlock blk) {
+  static_assert(!WHOLE || (ROWS && T::IMGS == 1 && !T::NARROW), "whole-image tiles are full-width");
   extern __shared__ float lds[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -341,7 +358,52 @@ __global__ __launch_bounds__(256, 2) void conv3x3_wgrad_f32(WgArgs a) {
 
   float rdy[T::DY_PT], rx[T::X_PT];
 
+  // Full-width tiles: each element's offset in its image for a tile at row
+  // 0, and its row in the tile (dy) or halo (x); a row of kNone marks an
+  // element that no tile has (k, channel or column outside, or past the
+  // staged range).
+  static_assert(!ROWS || T::IMGS == 1, "one image per full-width tile");
+  constexpr int kNone = 1 << 20;
+  int dy_rel[ROWS ? T::DY_PT : 1], dy_row[ROWS ? T::DY_PT : 1];
+  int x_rel[ROWS ? T::X_PT : 1], x_row[ROWS ? T::X_PT : 1];
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int i = 0; i < T::DY_PT; ++i) {
+      const int e = tid + i * 256;
+      const int kk = (e >> 2) & (T::BK - 1), p = ((e >> 8) << 2) | (e & 3);
+      const int yy = p / T::TW, xx = p % T::TW;
+      dy_rel[i] = (k0 + kk) * HWs + yy * a.W + xx;
+      dy_row[i] = k0 + kk < a.K ? yy : kNone;
+    }
+#pragma unroll
+    for (int i = 0; i < T::X_PT; ++i) {
+      const int e = tid + i * 256;
+      const int hp = e / T::BC, cc = e - hp * T::BC;
+      const int hy = hp / T::HW, w = hp % T::HW - 1, c = c0 + cc;
+      const bool ok = e < T::BC * T::PLANE && c < a.C && (unsigned)w < (unsigned)a.W;
+      x_rel[i] = c * HWs + (hy - 1) * a.W + w;
+      x_row[i] = ok ? hy - 1 : kNone;
+    }
+  }
+
   auto gload = [&](int pt) {
+    if constexpr (ROWS) {
+      const int ty = pt % a.tiles_h, n0 = pt / a.tiles_h;
+      const int h0 = ty * T::TH, hoff = h0 * a.W;
+      const rsrc_t dr = image_rsrc<E>(a.dy, n0, 1, a.N, a.K * HWs);
+      const rsrc_t xr = image_rsrc<E>(a.x, n0, 1, a.N, a.C * HWs);
+#pragma unroll
+      for (int i = 0; i < T::DY_PT; ++i)
+        rdy[i] = BufLoad<E>::one(dr, h0 + dy_row[i] < a.H
+                                         ? (uint32_t)(dy_rel[i] + hoff) * (uint32_t)sizeof(E)
+                                         : kOOB);
+#pragma unroll
+      for (int i = 0; i < T::X_PT; ++i)
+        rx[i] = BufLoad<E>::one(xr, (unsigned)(h0 + x_row[i]) < (unsigned)a.H
+                                        ? (uint32_t)(x_rel[i] + hoff) * (uint32_t)sizeof(E)
+                                        : kOOB);
+      return;
+    }
     int tx = pt % a.tiles_w, r0 = pt / a.tiles_w;
     int ty = r0 % a.tiles_h, tn = r0 / a.tiles_h;
     const int n0 = tn * T::IMGS, h0 = ty * T::TH, w0 = tx * T::TW;
@@ -411,7 +473,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_wgrad_f32(WgArgs a) {
 #pragma unroll
       for (int t = 0; t < T::NACC; ++t) {
         const int toff = (t / 3) * T::HW + (t % 3);
-        o.b[t] = Xp[toff * T::BC + lr];
+        o.b[t] = wg_pad_step<T, WHOLE>(st, t) ? 0.f : Xp[toff * T::BC + lr];
       }
     }
     return o;
@@ -426,7 +488,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_wgrad_f32(WgArgs a) {
       if (st + 1 < T::BP / 4) nxt = fetch(Dl, Xl, st + 1);
 #pragma unroll
       for (int t = 0; t < T::NACC; ++t)
-        acc[t] = mfma16x16x4(cur.a, cur.b[t], acc[t]);
+        if (!wg_pad_step<T, WHOLE>(st, t)) acc[t] = mfma16x16x4(cur.a, cur.b[t], acc[t]);
       sbias += cur.a;
       if (st + 1 < T::BP / 4) cur = nxt;
     }
@@ -464,6 +526,36 @@ __global__ __launch_bounds__(256, 2) void conv3x3_wgrad_f32(WgArgs a) {
         int c = c0 + lr;
         return c < a.C ? c * 9 + t : -1;
       });
+}
+
+template <class T, class E, bool ROWS = false, bool WHOLE = false>
+__global__ __launch_bounds__(256, 2) void conv3x3_wgrad_f32(WgArgs a) {
+  wgrad_f32_block<T, E, ROWS, WHOLE>(a, wg_block());
+}
+
+// Weight gradients of up to kWgMany layers that take the same kernel, in
+// one launch: layer i owns the blocks first[i] .. first[i+1]-1 of a 1-D
+// grid, numbered within the layer as wg_block numbers a layer's own grid
+// (dealt to the XCDs in whole splits when its block count and its first
+// block are multiples of 8).  One launch instead of one per layer lets the
+// next layer's blocks start while the previous layer's last blocks drain.
+constexpr int kWgMany = 4;
+struct WgMany {
+  WgArgs a[kWgMany];
+  int first[kWgMany + 1];   // first block of each layer, then the total
+  int gx[kWgMany];          // the layer's column blocks (its grid's x extent)
+  int n;
+};
+
+template <class T, class E, bool ROWS, bool WHOLE>
+__global__ __launch_bounds__(256, 2) void conv3x3_wgrad_f32_many(WgMany m) {
+  const int b = blockIdx.x;
+  int i = 0;
+  while (i + 1 < m.n && b >= m.first[i + 1]) ++i;
+  const int nb = m.first[i + 1] - m.first[i], gx = m.gx[i];
+  int h = b - m.first[i];
+  if (nb % 8 == 0 && m.first[i] % 8 == 0) h = (h % 8) * (nb / 8) + h / 8;
+  wgrad_f32_block<T, E, ROWS, WHOLE>(m.a[i], WgBlock{h % gx, h / gx});
 }
 
 // --------------------------------------------------------- bf16 MFMA --
@@ -1468,12 +1560,12 @@ static void wg_launch_2x2(const WgPlan& p, const WgArgs& a, hipStream_t st) {
   if (p.splits > 1) launch_splits_reduce(a.part, p.splits, a.K, a.C, a.dw, a.db, st);
 }
 
-template <class T, bool SMALL, class E>
+template <class T, bool SMALL, class E, bool ROWS = false, bool WHOLE = false>
 static void wg_launch(const WgPlan& p, const WgArgs& a, hipStream_t st) {
   static bool attr_set = false;
   const void* fn;
   if constexpr (SMALL) fn = (const void*)conv3x3_wgrad_small_f32<T, E>;
-  else fn = (const void*)conv3x3_wgrad_f32<T, E>;
+  else fn = (const void*)conv3x3_wgrad_f32<T, E, ROWS, WHOLE>;
   if (!attr_set) {
     (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
     attr_set = true;
@@ -1482,8 +1574,33 @@ static void wg_launch(const WgPlan& p, const WgArgs& a, hipStream_t st) {
   if constexpr (SMALL)
     conv3x3_wgrad_small_f32<T, E><<<grid, 256, T::LDS_BYTES, st>>>(a);
   else
-    conv3x3_wgrad_f32<T, E><<<grid, 256, T::LDS_BYTES, st>>>(a);
+    conv3x3_wgrad_f32<T, E, ROWS, WHOLE><<<grid, 256, T::LDS_BYTES, st>>>(a);
   if (p.splits > 1) launch_splits_reduce(a.part, p.splits, a.K, a.C, a.dw, a.db, st);
+}
+
+// n (<= kWgMany) layers' weight gradients on one launch of
+// conv3x3_wgrad_f32_many, then each layer's split reduction in layer order.
+template <class T, class E, bool ROWS, bool WHOLE>
+static void wg_launch_many(const WgPlan* p, const WgArgs* a, int n, hipStream_t st) {
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute((const void*)conv3x3_wgrad_f32_many<T, E, ROWS, WHOLE>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
+  });
+  WgMany m{};
+  m.n = n;
+  int total = 0;
+  for (int i = 0; i < n; ++i) {
+    m.a[i] = a[i];
+    m.first[i] = total;
+    m.gx[i] = p[i].k_tiles * p[i].c_tiles;
+    total += m.gx[i] * p[i].splits;
+  }
+  for (int i = n; i <= kWgMany; ++i) m.first[i] = total;
+  conv3x3_wgrad_f32_many<T, E, ROWS, WHOLE><<<total, 256, T::LDS_BYTES, st>>>(m);
+  for (int i = 0; i < n; ++i)
+    if (p[i].splits > 1)
+      launch_splits_reduce(a[i].part, p[i].splits, a[i].K, a[i].C, a[i].dw, a[i].db, st);
 }
 
 }  // namespace sb
@@ -1506,6 +1623,10 @@ size_t conv_wgrad_split_ws(int N, int C, int H, int W, int K);
 int conv_wgrad_split_describe(int N, int C, int H, int W, int K, char* buf, size_t len);
 sb_status conv_wgrad_split(int N, int C, int H, int W, int K, const void* x, const void* dy,
                            float* dw, float* db, void* ws, size_t ws_bytes, hipStream_t st);
+int conv_wgrad_split_key(int N, int C, int H, int W, int K, const void* x, const void* dy);
+sb_status conv_wgrad_split_group(int n, const int (*shape)[5], const void* const* x,
+                                 const void* const* dy, float* const* dw, float* const* db,
+                                 void* const* ws, const size_t* ws_bytes, hipStream_t st);
 void conv_wgrad_reduce(const float* part, int splits, int K, int C, float* dw, float* db,
                        hipStream_t st) {
   sb::launch_splits_reduce(part, splits, K, C, dw, db, st);
@@ -1566,10 +1687,27 @@ template <class E>
 static void wg_dispatch(const sb::WgPlan& p, const sb::WgArgs& a, hipStream_t st) {
   constexpr bool F32 = sizeof(E) == 4;
   switch (p.tile) {
-    // fp32 only: bf16 plans of these tiles run on the bf16 MFMA.
-    case 0: if constexpr (F32) sb::wg_launch<sb::WgW32, false, E>(p, a, st); break;
-    case 1: if constexpr (F32) sb::wg_launch<sb::WgW16, false, E>(p, a, st); break;
-    case 2: if constexpr (F32) sb::wg_launch<sb::WgW8, false, E>(p, a, st); break;
+    // fp32 only: bf16 plans of these tiles run on the bf16 MFMA.  Images exactly
+    // as wide as the tile take the full-width staging.
+    case 0:
+      if constexpr (F32) {
+        if (a.W == 32) sb::wg_launch<sb::WgW32, false, E, true>(p, a, st);
+        else sb::wg_launch<sb::WgW32, false, E>(p, a, st);
+      }
+      break;
+    case 1:
+      if constexpr (F32) {
+        if (a.W == 16) sb::wg_launch<sb::WgW16, false, E, true>(p, a, st);
+        else sb::wg_launch<sb::WgW16, false, E>(p, a, st);
+      }
+      break;
+    case 2:
+      if constexpr (F32) {
+        if (a.W == 8 && a.H == 8) sb::wg_launch<sb::WgW8, false, E, true, true>(p, a, st);
+        else if (a.W == 8) sb::wg_launch<sb::WgW8, false, E, true>(p, a, st);
+        else sb::wg_launch<sb::WgW8, false, E>(p, a, st);
+      }
+      break;
     case 3: sb::wg_launch<sb::WgW4, false, E>(p, a, st); break;
     case 4: sb::wg_launch<sb::WgW2, false, E>(p, a, st); break;
     case 5: sb::wg_launch<sb::WgN32_2, false, E>(p, a, st); break;
@@ -1617,6 +1755,67 @@ sb_status conv_wgrad(int dtype, int N, int C, int H, int W, int K, const void* x
     wg_dispatch<sb::u16>(p, a, st);
   } else {
     wg_dispatch<float>(p, a, st);
+  }
+  return launch_status();
+}
+
+// Batch key of an NCHW weight gradient: layers whose plan runs the same
+// conv3x3_wgrad_f32 instantiation (fp32, wide tiles; keys from 16 up) or the
+// same split one (0..5) share a key; -1 for a layer that takes another kernel
+// (it runs on its own).
+int conv_wgrad_batch_key(int dtype, int N, int C, int H, int W, int K, const void* x,
+                         const void* dy) {
+  if (dtype != SB_F32) return -1;
+  if (conv_wgrad_split_takes(N, C, H, W, K)) return conv_wgrad_split_key(N, C, H, W, K, x, dy);
+  const bool aligned = (((uintptr_t)x | (uintptr_t)dy) & 15) == 0;
+  const sb::WgPlan p = sb::wg_plan(N, C, H, W, K, aligned, false);
+  if (p.bc != 0 || p.tile > 2) return -1;
+  if ((int64_t)std::min(p.imgs, N) * std::max(C, K) * H * W * 4 >= (1ll << 31)) return -1;
+  const bool rows = (p.tile == 0 && W == 32) || (p.tile == 1 && W == 16) ||
+                    (p.tile == 2 && W == 8);
+  const bool whole = p.tile == 2 && W == 8 && H == 8;
+  return 16 + p.tile * 4 + (rows ? 2 : 0) + (whole ? 1 : 0);
+}
+
+// n (1..4) layers with one batch key on one launch: the same partials,
+// reductions and results as n conv_wgrad calls.  shape[i] = {N, C, H, W, K};
+// ws[i] / ws_bytes[i]: layer i's own workspace region.
+sb_status conv_wgrad_group(int n, const int (*shape)[5], const void* const* x,
+                           const void* const* dy, float* const* dw, float* const* db,
+                           void* const* ws, const size_t* ws_bytes, hipStream_t st) {
+  if (n < 1 || n > sb::kWgMany) return SB_ERR_INVALID_ARG;
+  if (conv_wgrad_split_takes(shape[0][0], shape[0][1], shape[0][2], shape[0][3], shape[0][4]))
+    return conv_wgrad_split_group(n, shape, x, dy, dw, db, ws, ws_bytes, st);
+  sb::WgPlan p[sb::kWgMany];
+  sb::WgArgs a[sb::kWgMany];
+  int key = -2;
+  for (int i = 0; i < n; ++i) {
+    const int N = shape[i][0], C = shape[i][1], H = shape[i][2], W = shape[i][3],
+              K = shape[i][4];
+    const int k = conv_wgrad_batch_key(SB_F32, N, C, H, W, K, x[i], dy[i]);
+    if (k < 0 || (key != -2 && k != key)) return SB_ERR_INVALID_ARG;
+    key = k;
+    const bool aligned = (((uintptr_t)x[i] | (uintptr_t)dy[i]) & 15) == 0;
+    p[i] = sb::wg_plan(N, C, H, W, K, aligned, false);
+    if (p[i].ws_bytes > 0 && (ws[i] == nullptr || ws_bytes[i] < p[i].ws_bytes))
+      return SB_ERR_WORKSPACE;
+    sb::WgArgs& g = a[i];
+    g = sb::WgArgs{};
+    g.x = x[i]; g.dy = dy[i]; g.dw = dw[i]; g.db = db ? db[i] : nullptr;
+    g.part = p[i].splits > 1 ? (float*)ws[i] : nullptr;
+    g.N = N; g.C = C; g.H = H; g.W = W; g.K = K;
+    g.tiles_w = p[i].tiles_w; g.tiles_h = p[i].tiles_h; g.ptiles = p[i].ptiles;
+    g.tiles_per_split = p[i].tps; g.c_tiles = p[i].c_tiles; g.splits = p[i].splits;
+  }
+  switch (key) {
+    case 16: sb::wg_launch_many<sb::WgW32, float, false, false>(p, a, n, st); break;
+    case 18: sb::wg_launch_many<sb::WgW32, float, true, false>(p, a, n, st); break;
+    case 20: sb::wg_launch_many<sb::WgW16, float, false, false>(p, a, n, st); break;
+    case 22: sb::wg_launch_many<sb::WgW16, float, true, false>(p, a, n, st); break;
+    case 24: sb::wg_launch_many<sb::WgW8, float, false, false>(p, a, n, st); break;
+    case 26: sb::wg_launch_many<sb::WgW8, float, true, false>(p, a, n, st); break;
+    case 27: sb::wg_launch_many<sb::WgW8, float, true, true>(p, a, n, st); break;
+    default: return SB_ERR_INVALID_ARG;
   }
   return launch_status();
 }

@@ -18,7 +18,9 @@
 // sums of 32 pixels are off by a little with the same sign and over 1e5 pixels
 // that adds up (dw of 128 images of 32x32 against 64 bits: 4.4e-7, on the fp32
 // MFMA 4.0e-7).  dy is therefore negated for the odd waves' pixels as it is
-// staged, and their sums are subtracted: the shares cancel (1.2e-7).
+// staged, and their sums are subtracted: the shares cancel (1.2e-7).  (Flipped
+// as the multiplying waves read it, their registers spill: 193 -> 213 us for a
+// 32x32 layer's three passes.)
 //
 //   * Staging: a lane loads 8 channels of 4 consecutive pixels as fp32 NCHW
 //     (16-byte loads where rows are whole aligned quads), splits them, and
@@ -527,16 +529,26 @@ void conv_wgrad_reduce(const float* part, int splits, int K, int C, float* dw, f
                        hipStream_t st);
 
 // Whether an fp32 weight gradient runs here: at least 8 input channels (the
-// narrow kernels flatten fewer), images at least 4 wide, and enough work for
-// 128-pixel tiles where they suit the image less.  With v = pixels x C x K:
-// narrower than 8, from 1.4e7 on (100 images of 4x6, 64 channels, 9.8e6: 15 us
-// on the fp32 MFMA, 20 here; 64 of 5x7, 100 -> 75, 1.7e7: 26, 20); rows that
-// are not whole quads (4-byte loads), from 7e6 on (8 images of 24x17, 32 -> 40,
-// 4.2e6: 14.4, 16.2; 30 of 9x11, 16 -> 200, 9.5e6: 22, 19); any other.
+// narrow kernels flatten fewer), images at least 4 wide, 4x4 ones at least 8 (a
+// tile), and enough work, which is counted as the fp32 MFMA would do it: u =
+// padded pixels (tiles of 2x32, 4x16, 8x8, or 4 images of 4x4) x 64-channel tiles x
+// 16-channel tiles.  From 1.65e7 on, from 1.5e7 on narrow images: of 678 layers
+// of 3e5 to 2e8 products 9 are then slower than on the fp32 MFMA, by 17 % at most
+// (55 images of 36x36, 32 -> 64: 61 us, 72), where a line at 7e6 products or none had 70
+// (12 images of 8x8, 72 -> 24: u = 3.9e6, 9.5 us on the fp32 MFMA, 11.9 here; 5 of
+// 28x36, 64 -> 16: 2.3e7, 20.7 and 12.9; 4 of 4x4, 512 -> 512: 7.0 and 11.3).  The
+// fp32 MFMA's 4x4 kernel wastes less on few channels, so 4x4 images also need
+// 1.4e7 products (128 of them, 128 -> 24, 6.3e6: 9.5 and 12.6).
 bool conv_wgrad_split_takes(int N, int C, int H, int W, int K) {
-  if (C < 8 || W < 4) return false;
-  const double v = (double)N * H * W * C * K;
-  return W < 8 ? v >= 1.4e7 : W % 4 == 0 || v >= 7e6;
+  using sb::cdiv;
+  if (C < 8 || W < 4 || (W == 4 && H == 4 && N < 8)) return false;
+  long tiles;
+  if (W >= 32) tiles = (long)N * cdiv(W, 32) * cdiv(H, 2);
+  else if (W >= 16) tiles = (long)N * cdiv(W, 16) * cdiv(H, 4);
+  else if (W >= 8) tiles = (long)N * cdiv(W, 8) * cdiv(H, 8);
+  else tiles = (long)cdiv(N, 4) * cdiv(W, 4) * cdiv(H, 4);
+  const double u = (double)tiles * 64 * (cdiv(K, 64) * 64.0) * (cdiv(C, 16) * 16.0);
+  return u >= (W < 8 ? 1.5e7 : 1.65e7) && (H != 4 || W != 4 || 16.0 * N * C * K >= 1.4e7);
 }
 
 size_t conv_wgrad_split_ws(int N, int C, int H, int W, int K) {
@@ -566,12 +578,9 @@ sb_status conv_wgrad_split(int N, int C, int H, int W, int K, const void* x, con
   return launch_status();
 }
 
-// Batch key of an NCHW weight gradient: layers on the same instantiation of
-// the kernel above share a key; -1 for a layer that takes another kernel or
-// that the kernel refuses (it runs on its own).
-int conv_wgrad_batch_key(int dtype, int N, int C, int H, int W, int K, const void* x,
-                         const void* dy) {
-  if (dtype != SB_F32 || !conv_wgrad_split_takes(N, C, H, W, K)) return -1;
+// Batch key (0..5) of a layer that runs here: layers on the same instantiation
+// of the kernel above share a key; -1 for a layer that the kernel refuses.
+int conv_wgrad_split_key(int N, int C, int H, int W, int K, const void* x, const void* dy) {
   const sb::WsPlan p = sb::ws_plan(N, C, H, W, K);
   if ((int64_t)std::min(p.imgs, N) * std::max(C, K) * H * W * 4 >= (1ll << 31)) return -1;
   return p.tile * 2 + (sb::ws_vec(W, x, dy) ? 1 : 0);
@@ -580,9 +589,9 @@ int conv_wgrad_batch_key(int dtype, int N, int C, int H, int W, int K, const voi
 // n (1..4) layers with one batch key on one launch: the same partials,
 // reductions and results as n single calls.  shape[i] = {N, C, H, W, K};
 // ws[i] / ws_bytes[i]: layer i's own workspace region.
-sb_status conv_wgrad_group(int n, const int (*shape)[5], const void* const* x,
-                           const void* const* dy, float* const* dw, float* const* db,
-                           void* const* ws, const size_t* ws_bytes, hipStream_t st) {
+sb_status conv_wgrad_split_group(int n, const int (*shape)[5], const void* const* x,
+                                 const void* const* dy, float* const* dw, float* const* db,
+                                 void* const* ws, const size_t* ws_bytes, hipStream_t st) {
   if (n < 1 || n > sb::kWsMany) return SB_ERR_INVALID_ARG;
   sb::WsPlan p[sb::kWsMany];
   sb::WsMany m{};
@@ -591,7 +600,8 @@ sb_status conv_wgrad_group(int n, const int (*shape)[5], const void* const* x,
   for (int i = 0; i < n; ++i) {
     const int N = shape[i][0], C = shape[i][1], H = shape[i][2], W = shape[i][3],
               K = shape[i][4];
-    const int k = conv_wgrad_batch_key(SB_F32, N, C, H, W, K, x[i], dy[i]);
+    if (!conv_wgrad_split_takes(N, C, H, W, K)) return SB_ERR_INVALID_ARG;
+    const int k = conv_wgrad_split_key(N, C, H, W, K, x[i], dy[i]);
     if (k < 0 || (i > 0 && k != key)) return SB_ERR_INVALID_ARG;
     key = k;
     p[i] = sb::ws_plan(N, C, H, W, K);

@@ -228,7 +228,8 @@ class ConvStack:
         host-side queries only."""
         def name(d):
             s = sb.sb_conv3x3_plan_string(d, sb.SB_PASS_BWD_WEIGHT).split(" grid=")[0]
-            return s if re.fullmatch(r"sb::conv3x3_wgrad_split<sb::WsTile<\d+, \d+, \d+>, \w+>",
+            return s if re.fullmatch(r"sb::conv3x3_wgrad_split<sb::WsTile<\d+, \d+, \d+>, \w+>|"
+                                     r"sb::conv3x3_wgrad_f32<sb::WgTile<\d+, \d+, \d+, 0>, float>",
                                      s) else None
         groups, run = [], []
         for i in reversed(range(len(descs))):

@@ -24,7 +24,8 @@ SHAPES = [(27, 95, 9, 33, 26), (43, 29, 9, 40, 27), (27, 24, 9, 33, 90), (22, 37
           (76, 18, 8, 16, 129), (149, 20, 4, 16, 64), (65, 82, 8, 9, 106), (19, 18, 16, 33, 67),
           (17, 246, 9, 16, 67), (59, 139, 16, 8, 16), (36, 70, 30, 8, 20), (50, 19, 16, 8, 157),
           (4, 151, 9, 20, 369), (29, 36, 30, 8, 48), (51, 99, 5, 5, 317), (40, 65, 9, 8, 217),
-          (72, 22, 30, 8, 32), (39, 397, 8, 5, 66), (40, 50, 14, 14, 60)]
+          (72, 22, 30, 8, 32), (39, 397, 8, 5, 66), (40, 50, 14, 14, 60), (21, 223, 5, 5, 50),
+          (80, 18, 9, 5, 290), (161, 92, 8, 5, 27), (110, 26, 9, 6, 102)]
 PASSES = (sb.SB_PASS_FWD, sb.SB_PASS_BWD_DATA, sb.SB_PASS_BWD_WEIGHT)
 
 
@@ -42,19 +43,25 @@ def test_shapes_reach_every_tile():
     assert len([s for s in seen if "conv3x3_wgrad_split" in s]) == 6, seen
 
 
+# f, d, w: the pass runs on the split kernel.  Times in us, fp32 MFMA and split.
 @pytest.mark.parametrize("shape,passes", [
-    ((8, 128, 16, 16, 128), "--w"),      # 2048 pixels, 3.4e7 products: below 4e7
-    ((24, 64, 16, 16, 64), "fdw"),       # 6144 pixels, 2.5e7
-    ((24, 64, 16, 15, 64), "--w"),       # 5760 pixels
+    ((16, 512, 4, 4, 512), "fdw"),       # forward and data gradient 85, 64
+    ((8, 512, 4, 4, 512), "fdw"),
+    ((4, 512, 4, 4, 512), "fd-"),        # weight gradient 7.0, 11.3: half a tile of images
+    ((24, 64, 16, 16, 64), "--w"),       # 64-channel blocks of 3 rounds
+    ((74, 24, 20, 20, 32), "-dw"),       # one chunk: forward 23, 31
+    ((128, 32, 8, 8, 256), "fdw"),
     ((64, 24, 32, 32, 16), "--w"),       # 16 outputs; the data gradient has 16 inputs
-    ((64, 16, 32, 32, 64), "--w"), # a chunk is 32 channels; the gradient has 16 outputs
-    ((16, 512, 4, 4, 512), "fdw"),
-    ((8, 512, 4, 4, 512), "--w"),        # 3.4e7 on narrow images
+    ((64, 16, 32, 32, 64), "--w"),       # a chunk is 32 channels; the gradient has 16 outputs
     ((128, 512, 2, 2, 512), "---"),
-    ((8, 32, 24, 17, 40), "---"),        # rows of broken quads, below 7e6
-    ((8, 32, 24, 16, 40), "--w"),
-    ((100, 64, 4, 6, 64), "---"),        # narrow images, below 1.4e7
     ((128, 3, 32, 32, 64), "---"),
+    ((12, 64, 8, 8, 16), "---"),         # weight gradients: 9.2, 11.9
+    ((2, 40, 15, 16, 32), "---"),        # 9.1, 11.5
+    ((8, 32, 24, 16, 40), "---"),
+    ((5, 64, 28, 36, 16), "--w"),        # 20.7, 12.9: rows of 64 on the fp32 MFMA
+    ((8, 32, 24, 17, 40), "-d-"),        # rows of broken quads: weight gradient 14.4, 16.2
+    ((24, 64, 16, 15, 64), "--w"),
+    ((100, 64, 4, 6, 64), "---"),        # narrow images: 15, 20
 ])
 def test_rule(shape, passes):
     for p, want in zip(PASSES, passes):
@@ -160,9 +167,14 @@ def test_conv_values_the_split_cannot_carry(shape):
         assert rel_l2(a[ok], r[ok]) < 1e-5, name
 
 
+POOL_SHAPES = [(24, 64, 16, 16, 64), (33, 256, 4, 4, 300), (18, 68, 30, 8, 136), (28, 69, 4, 40, 78),
+               (1, 346, 2, 4, 1), (288, 52, 4, 4, 1), (66, 177, 6, 12, 1), (69, 65, 16, 12, 1),
+               (91, 28, 2, 6, 494), (42, 135, 2, 6, 235), (23, 73, 4, 20, 227), (255, 28, 4, 4, 277),
+               (139, 80, 8, 4, 208)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", [(24, 64, 16, 16, 64), (33, 256, 4, 4, 300), (18, 68, 30, 8, 136),
-                                   (28, 69, 4, 40, 78)])
+@pytest.mark.parametrize("shape", POOL_SHAPES)
 def test_pooled_forward_is_the_forward_pooled(shape):
     print_case("split conv pool", shape=shape)
     n, c, h, wd, k = shape
