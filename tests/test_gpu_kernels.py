@@ -87,6 +87,12 @@ CONV_SHAPES = [
     (1, 9, 3, 64, 2),
     (1, 1, 1, 1, 1),         # degenerate: every tap but the centre is padding
     (1, 9, 3, 1, 5),
+    # the forms that the shapes above leave out (tests/test_plan_coverage.py):
+    # 4x4 and 2x2 tiles, whole and split; wide rows of few channels; the large
+    # 8x32 tile; two-group 8x8 blocks over many images
+    (1, 16, 1, 4, 1), (1, 5, 4, 4, 5), (1, 26, 1, 1, 35), (1, 4, 3, 34, 8), (1, 23, 1, 34, 8),
+    (1, 1, 1, 16, 1), (1, 1, 2, 2, 5), (1, 1, 1, 36, 6), (1, 5, 1, 34, 37), (1, 30, 3, 34, 6),
+    (312, 25, 1, 12, 3), (295, 3, 1, 12, 29), (358, 7, 1, 34, 19), (426, 18, 1, 34, 8),
 ]
 
 
@@ -360,15 +366,20 @@ def test_conv_pack_filters_many_matches_single(dtype):
         assert torch.equal(many, one), (d.n, d.c, d.h, d.w, d.k, p_)
 
 
-# Forward with fused ReLU + 2x2 pooling on NCHW fp32 (sb_conv3x3_fwd_pool):
-# unsplit plans pooling in the epilogue (4x32 tiles, 8x16 tiles with two
-# channel tiles, the two-group 8x8 tiles on whole 8x8 images, the same tiles
-# over 14x14 images: ragged tiles and pooled edge) and split plans pooling in
-# the split reduction (a small batch, the whole-image 4x4 and 2x2 tiles, a
-# ragged output-channel tile).
-FUSED_F32_SHAPES = [(64, 64, 32, 32, 64), (128, 64, 16, 16, 128), (128, 128, 8, 8, 256),
-                    (128, 64, 14, 14, 64), (2, 64, 32, 32, 64), (128, 512, 4, 4, 512),
-                    (128, 512, 2, 2, 512), (33, 64, 2, 2, 130), (33, 40, 4, 4, 70)]
+# Forward with fused ReLU + 2x2 pooling on NCHW fp32 (sb_conv3x3_fwd_pool).
+FUSED_F32_SHAPES = [
+    # split kernels pooling in the epilogue and in the split reduction
+    (64, 64, 32, 32, 64), (128, 64, 16, 16, 128), (128, 128, 8, 8, 256), (128, 64, 14, 14, 64),
+    (2, 64, 32, 32, 64), (128, 512, 4, 4, 512), (33, 40, 4, 4, 70),
+    # 2x2 images
+    (128, 512, 2, 2, 512), (33, 64, 2, 2, 130),
+    # fp32-MFMA tiles pooling in the epilogue: 4x32 (3 and 8 channels a chunk), 8x32,
+    # 8x16, 8x8 over whole images, 14x14 and 12 wide ones, the two-group blocks
+    (2, 3, 4, 36, 20), (1, 5, 2, 36, 18), (128, 8, 32, 32, 64), (128, 16, 16, 16, 128),
+    (128, 16, 8, 8, 256), (128, 16, 14, 14, 64), (2, 5, 8, 8, 20), (3, 4, 6, 12, 20),
+    (330, 28, 8, 14, 1), (270, 37, 16, 8, 1),
+    # and in the split reduction
+    (1, 34, 6, 2, 3), (2, 30, 2, 4, 5), (1, 41, 2, 14, 3), (1, 60, 2, 36, 5)]
 
 
 @pytest.mark.parametrize("shape", FUSED_F32_SHAPES, ids=lambda s: "x".join(map(str, s)))
