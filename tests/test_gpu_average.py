@@ -38,7 +38,9 @@ def test_model_average(workers, mp, n, stride):
 
 
 @pytest.mark.parametrize("replicas,n,offset", [(2, 1000, 0), (3, 1001, 0), (5, 4096, 1),
-                                               (8, 1 << 16, 0), (1, 100, 0)])
+                                               (8, 1 << 16, 0), (1, 100, 0), (4, 4099, 0),
+                                               (4, 4096, 0), (6, 257, 3), (7, 1 << 12, 0),
+                                               (7, 1001, 1), (9, 1001, 1), (12, 2048, 0)])
 def test_model_average_replicas(replicas, n, offset):
     """Replicas in separate buffers (offset: elements past a 16-byte boundary,
     the element-wise path); every buffer gets the mean, the bytes around
