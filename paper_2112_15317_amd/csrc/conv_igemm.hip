@@ -872,8 +872,6 @@ using TileW2 = ConvTile<2, 2, 32, 8, 64, 2>;
 using TileW32c4 = ConvTile<4, 32, 1, 4, 64, 2, 1, 1>;   // output staged through LDS
 using TileW32n16 = ConvTile<4, 32, 1, 8, 16, 1>;
 using TileW32L = ConvTile<8, 32, 1, 8, 64, 1, 1, 1>;
-using TileW16L = ConvTile<16, 16, 1, 8, 64, 1, 1, 1>;
-using TileW8L = ConvTile<8, 8, 4, 8, 64, 1, 1, 1>;
 using TileW8K2 = ConvTile<8, 8, 2, 8, 64, 2, 2, 1>;
 using Small2 = SmallTile<2, 2, 2>;
 using Small4 = SmallTile<4, 4, 1>;
@@ -891,8 +889,6 @@ static const char* kTileNames[] = {
     "sb::conv3x3_small_f32<sb::SmallTile<2, 2, 2, 1>, %s, %s>",
     "sb::conv3x3_small_f32<sb::SmallTile<4, 4, 1, 1>, %s, %s>",
     "sb::conv3x3_igemm_f32<sb::ConvTile<8, 32, 1, 8, 64, 1, 1, 1>, %s, %s>",
-    "sb::conv3x3_igemm_f32<sb::ConvTile<16, 16, 1, 8, 64, 1, 1, 1>, %s, %s>",
-    "sb::conv3x3_igemm_f32<sb::ConvTile<8, 8, 4, 8, 64, 1, 1, 1>, %s, %s>",
     "sb::conv3x3_igemm_f32<sb::ConvTile<8, 8, 2, 8, 64, 2, 2, 1>, %s, %s>",
     "sb::conv3x3_small_f32<sb::SmallTile<2, 2, 2, 2>, %s, %s>",
     "sb::conv3x3_small_f32<sb::SmallTile<4, 4, 1, 2>, %s, %s>",
@@ -923,11 +919,11 @@ static IgemmPlan igemm_plan(int N, int Cin, int H, int W, int Cout, int esize,
   long blocks = (long)p.grid_x * p.co_tiles;
   // 8x8-image tiles that cannot fill the chip take the two-group block
   // (intra-block split over channel chunks) before any split in HBM.
-  if (p.tile == 2 && blocks < 512 && p.nchunks >= 4) { p.tile = 12; blocks *= 2; }
+  if (p.tile == 2 && blocks < 512 && p.nchunks >= 4) { p.tile = 10; blocks *= 2; }
   // Whole-image tiles likewise: two groups per block halve the split
   // partials written to and read back from HBM.
   if ((p.tile == 7 || p.tile == 8) && blocks < 512 && p.nchunks >= 4) {
-    p.tile = p.tile == 7 ? 13 : 14;
+    p.tile = p.tile == 7 ? 11 : 12;
     blocks *= 2;
   }
   // About two resident 256-thread groups on each of the 256 CUs; at most 8
@@ -1048,9 +1044,7 @@ inline bool igemm_pools(const IgemmPlan& p, int Cout) {
     case 2: return can_pool<TileW8, false, float>();
     case 5: return can_pool<TileW32c4, false, float>();
     case 9: return can_pool<TileW32L, false, float>();
-    case 10: return can_pool<TileW16L, false, float>();
-    case 11: return can_pool<TileW8L, false, float>();
-    case 12: return can_pool<TileW8K2, false, float>();
+    case 10: return can_pool<TileW8K2, false, float>();
     default: return false;
   }
 }
@@ -1089,10 +1083,8 @@ static void igemm_dispatch(const IgemmPlan& p, const ConvArgs& a, bool pack, hip
     case 7: igemm_launch<Small2, DGRAD, true, E>(p, a, pack, st); break;
     case 8: igemm_launch<Small4, DGRAD, true, E>(p, a, pack, st); break;
     case 9: igemm_launch<TileW32L, DGRAD, false, E>(p, a, pack, st); break;
-    case 10: igemm_launch<TileW16L, DGRAD, false, E>(p, a, pack, st); break;
-    case 11: igemm_launch<TileW8L, DGRAD, false, E>(p, a, pack, st); break;
-    case 12: igemm_launch<TileW8K2, DGRAD, false, E>(p, a, pack, st); break;
-    case 13: igemm_launch<Small2K2, DGRAD, true, E>(p, a, pack, st); break;
+    case 10: igemm_launch<TileW8K2, DGRAD, false, E>(p, a, pack, st); break;
+    case 11: igemm_launch<Small2K2, DGRAD, true, E>(p, a, pack, st); break;
     default: igemm_launch<Small4K2, DGRAD, true, E>(p, a, pack, st); break;
   }
 }
@@ -1249,7 +1241,7 @@ int conv_igemm_describe(bool dgrad, int dtype, int N, int Cin, int H, int W, int
     const size_t l = strlen(name);
     if (l > 0 && name[l - 1] == '>')
       snprintf(name + l - 1, sizeof(name) - (l - 1), ", %s, true>",
-               H == 8 && (p.tile == 2 || p.tile == 11 || p.tile == 12) ? "true" : "false");
+               H == 8 && (p.tile == 2 || p.tile == 10) ? "true" : "false");
   }
   return snprintf(buf, len, "%s grid=%dx%dx%d", name, p.grid_x, p.co_tiles, p.splits);
 }
