@@ -31,9 +31,9 @@
 //
 // Measured (us, batch 128, the fp32-MFMA kernel before): forward 32x32 64
 // channels 84 -> 54, 16x16 128 channels 82 -> 43, 8x8 256 channels 78 -> 40;
-// 27x45, 75 -> 107 channels, batch 19: 91 -> 38.  In the loop the matrix pipe
-// is 82 % busy at the 1.9 GHz that its power allows; the rest is the first
-// chunk's staging (2.5 us) and the output tile (2 to 4 us).
+// 27x45, 75 -> 107 channels, batch 19: 91 -> 38.  A call's first chunk is staged
+// before anything multiplies (2.5 us) and its output tile leaves after (2 to
+// 4 us); a grid of one round of blocks has nothing to put beside them.
 //
 // The data gradient is the same contraction with the filters transposed and
 // rotated (done by the packing).
@@ -577,7 +577,9 @@ static double fp32_mfma_us(int N, int Cin, int H, int W, int Cout) {
 // products that are padding), 16 input channels or fewer (a chunk is 32), wide
 // images of 16 output channels or fewer (a tile is 64), sizes whose offsets
 // pass 2^31 bytes.  Otherwise where the estimated time is the smaller one; a
-// pass of a single chunk has no loop to hide its first loads in (1.3 us).
+// pass of a single chunk has no loop to hide its first loads in (1.3 us).  Narrow
+// images of 4e7 products or more always run here, as only these tiles pool
+// where the reduction is not split.
 // Fitted to both kernels' times of 597 passes: the one taken is 0.5 % slower than
 // the faster one on average, and slower than the fp32 MFMA in 8, by 14 % at most
 // (a line by work and pixels alone: 5 %, 30, 33 %).  Forward and data gradient
@@ -591,6 +593,7 @@ bool conv_split_takes(int N, int Cin, int H, int W, int Cout) {
   if (4 * nchunks * sb::kSplitSlice * (int64_t)sizeof(sb::u16) >= (1ll << 31) ||
       (nchunks * 32 + 8) * H * W * 4 >= (1ll << 31))
     return false;
+  if (W < 8 && (double)N * H * W * Cin * Cout >= 4e7) return true;
   return fp32_mfma_us(N, Cin, H, W, Cout) >
          1.2 * sb::split_plan(N, Cin, H, W, Cout).us + (nchunks == 1 ? 1.3 : 0.0);
 }

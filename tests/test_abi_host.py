@@ -62,6 +62,14 @@ def test_filters_past_the_index_range_are_refused(pass_, image, reduce, out):
     assert r == sb.SB_ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("shape", [(565, 21, 6, 6, 280), (305, 46, 64, 4, 32), (531, 24, 4, 4, 391),
+                                   (350, 21, 10, 6, 132), (1200, 40, 6, 6, 60)])
+def test_narrow_images_of_few_channels_pool_in_the_call(shape):
+    # The fp32-MFMA tiles of images 4 to 7 wide pool only in a split reduction.
+    d = sb.conv_desc(*shape)
+    assert sb.sb_conv3x3_workspace_bytes(d, sb.SB_PASS_FWD_POOL) != sb.SIZE_MAX
+
+
 def test_offsets_past_the_split_range_take_the_fp32_mfma():
     # Four channel blocks' filters as bf16 triples pass 2^31 bytes from 621,376
     # input channels on; an image's last chunk of channels at 2^29 floats.

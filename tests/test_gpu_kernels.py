@@ -92,7 +92,8 @@ CONV_SHAPES = [
     # 8x32 tile; two-group 8x8 blocks over many images
     (1, 16, 1, 4, 1), (1, 5, 4, 4, 5), (1, 26, 1, 1, 35), (1, 4, 3, 34, 8), (1, 23, 1, 34, 8),
     (1, 1, 1, 16, 1), (1, 1, 2, 2, 5), (1, 1, 1, 36, 6), (1, 5, 1, 34, 37), (1, 30, 3, 34, 6),
-    (312, 25, 1, 12, 3), (295, 3, 1, 12, 29), (358, 7, 1, 34, 19), (426, 18, 1, 34, 8),
+    (2, 7, 5, 6, 25), (312, 25, 1, 12, 3), (295, 3, 1, 12, 29), (358, 7, 1, 34, 19),
+    (426, 18, 1, 34, 8),
 ]
 
 
