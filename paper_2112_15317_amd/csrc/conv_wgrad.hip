@@ -9,7 +9,9 @@
 // ALU (which runs beside the matrix pipe), and a butterfly over the lanes
 // completes the row sums; only blocks of the first column tile write them.
 // An MFMA against a column of ones in those blocks alone would make them
-// the slowest of the grid.  Three kernels:
+// the slowest of the grid.  Most fp32 layers run in conv_wgrad_split.hip
+// instead; small fp32 calls, 2x2 images, fewer than 8 input channels and bf16
+// tensors run here.  Three fp32-MFMA kernels:
 //
 // conv3x3_wgrad_f32 (any shape).  A block owns 64 k and walks a contiguous
 // range of 64-pixel tiles (IMGS images x TH rows x TW cols).  Per pixel tile

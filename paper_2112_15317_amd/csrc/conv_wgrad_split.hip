@@ -36,7 +36,9 @@
 // Measured (us, batch 128, the fp32-MFMA kernel before): 32x32 64 -> 64 channels
 // 97 -> 59, 16x16 128 channels 92 -> 54, 8x8 256 channels 87 -> 56, 4x4 512
 // channels 68 -> 53; 27x45, 75 -> 107 channels, batch 19: 79 -> 53.  With 4-byte
-// staging loads, 48 a lane and tile, the loads bound it (95 us at 16x16).
+// staging loads, 48 a lane and tile, the loads bound it (95 us at 16x16).  The
+// check for lost bits, one instruction in twelve of the split, costs large layers
+// of few output channels 4 to 6 % (128 images of 16x16, 512 -> 32: 93 -> 98).
 //
 // The pixels are split over blocks when the output tiles do not fill the 256
 // CUs; each split writes its sums to the workspace and they are added in split

@@ -13,11 +13,9 @@
 // stack's output is 4.6e-7 off instead of 6.9e-7; added straight into the
 // accumulator, six roundings per 32 terms, it was 7.8e-7, for 3 % less time.
 //
-// Six bf16 MFMAs of 16x16x32 take 0.38 of the time of the fp32 MFMAs of the
-// same product (which run at 155 TFLOP/s).  The matrix pipe is then limited by
-// power: over split random normals independent chains of the 16x16x32 form
-// sustain 2.0 PFLOP/s (clock 2.15 GHz), of the 32x32x16 form 1.73 (1.75 GHz),
-// and 1.80 when consecutive MFMAs share an operand.
+// Six bf16 MFMAs of 16x16x32 take 0.38 of the cycles of the fp32 MFMAs of the
+// same product.  Power then limits the matrix pipe: independent chains of the
+// 32x32x16 form run at 2.4 PFLOP/s over zeros and at 1.8 over random normals.
 //
 // Values the triple cannot carry.  An infinite or NaN operand, or one that
 // rounds to infinity (above 3.39e38), makes a NaN of every sum it enters.  bf16

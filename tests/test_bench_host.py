@@ -86,3 +86,22 @@ def test_committed_profiles_name_their_sources():
         text = open(p).read()
         assert re.search(r"^csrc_sha256: *[0-9a-f]{64}$", text, re.M), p
         assert re.search(r"^workload: *\S+", text, re.M), p
+
+
+def test_kernel_peak_is_that_of_the_instruction():
+    from paper_2112_15317_amd import sb
+    f32, split, bf16 = bench.PEAK_F32_MFMA_TFLOPS, 2500.0 / 6, 2500.0
+    for shape, dt, lay, want in (((128, 64, 32, 32, 64), "f32", sb.SB_NCHW, (split,) * 3),
+                                 ((128, 512, 2, 2, 512), "f32", sb.SB_NCHW, (f32,) * 3),
+                                 ((2, 24, 16, 16, 40), "f32", sb.SB_NCHW, (f32,) * 3),
+                                 ((128, 3, 32, 32, 64), "f32", sb.SB_NCHW, (f32,) * 3),
+                                 ((8, 64, 32, 32, 64), "bf16", sb.SB_NCHW8C, (bf16,) * 3),
+                                 ((8, 64, 32, 32, 64), "bf16", sb.SB_NCHW, (bf16,) * 3),
+                                 ((8, 64, 4, 4, 64), "bf16", sb.SB_NCHW, (f32,) * 3)):
+        d = sb.conv_desc(*shape, sb.SB_BF16 if dt == "bf16" else sb.SB_F32, layout=lay)
+        for p, w in zip((sb.SB_PASS_FWD, sb.SB_PASS_BWD_DATA, sb.SB_PASS_BWD_WEIGHT), want):
+            name = sb.sb_conv3x3_plan_string(d, p)
+            assert bench.kernel_peak(name, dt) == w, name
+    assert bench.kernel_peak("sb_fc_shard_fwd m=512 k_in=4096 n_shard=1024", "f32") == split
+    assert bench.kernel_peak("sb::conv3x3_wgrad_f32_many<sb::WgTile<8, 8, 1, 0>, float>", "f32") == f32
+    assert bench.kernel_peak("sb::conv3x3_wgrad_split_many<sb::WsTile<4, 4, 8>, true>", "f32") == split
