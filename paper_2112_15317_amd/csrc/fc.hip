@@ -600,16 +600,18 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
 //     one has it to itself; split partials a launch, `each`, and their traffic,
 //     `odd` times as much where outputs are added one by one.
 // Fitted to 15000 timings of the three products of 104 shards under forced plans
-// in both types: the plan taken is 0.8 % slower than the best one on average, 19 %
-// at most, where one block a CU at the same cost for all operands lost 4 % (fp32)
+// in both types; 1.7 and 1.2 us more for a launch, since a caller that does not
+// capture its calls is bound by them (K = 2 modulo iterations of 128 rows: 78
+// launches and 545 us, 70 and 517 without the splits that save less).  The plan
+// taken is 1.3 % slower than the best one on average, 19 % at most, where one block a CU at the same cost for all operands lost 4 % (fp32)
 // and 12 % (bf16), up to 2.1 times.
 struct GemmPlan { int bm, ko, mt, nt, splits, kps; size_t ws_bytes; };
 struct GemmCost { double block[2], k32[2], elems[2][3], alone, split, each, tb_s, odd; };
 static const GemmCost kGCost[2] = {
     {{3.44, 1.35}, {1.74, 1.08}, {{0.63, 1.28, 1.61}, {0.88, 1.17, 1.61}},       // fp32
-     0.68, 2.16, 0.11, 5.61, 1.58},
+     0.68, 3.86, 0.11, 5.61, 1.58},
     {{3.69, 1.30}, {0.95, 0.63}, {{1.28, 1.47, 2.17}, {1.37, 1.65, 2.91}},       // bf16
-     0.72, 2.50, 0.13, 5.24, 3.5}};
+     0.72, 3.70, 0.13, 5.24, 3.5}};
 
 // ak, bk: A, B contiguous along k; aligned: their rows allow vector staging.
 static GemmPlan gemm_plan(int M, int N, int K, int esize, bool ak, bool bk, bool aligned) {
@@ -623,16 +625,19 @@ static GemmPlan gemm_plan(int M, int N, int K, int esize, bool ak, bool bk, bool
     const int ks = ko * 8;                                   // k per stage
     const double elems = aligned ? 1.0 : c.elems[i][ak ? (bk ? 1 : 0) : 2];
     const int mt = cdiv(M, bm), nt = cdiv(N, bm), ktiles = cdiv(K, ks);
+    const double k32 = c.k32[i] * elems * ks / 32;
+    const int64_t tiles = (int64_t)mt * nt;
     for (int s = 1; s <= 32 && s <= ktiles; ++s) {
+      const double parts = s > 1 ? c.split + c.each * s + traffic * (2 * s + 1) : 0.0;
+      if (s > 1 && parts >= best_t) break;                   // and more with every split
       const int tps = cdiv(ktiles, s);
       if (cdiv(ktiles, tps) != s) continue;
       const bool two = b16 ? bm == 64 || tps * ks <= 32 * kGLocal : bm == 64 && ko == 4;
-      const long round = two ? 512 : 256, blocks = (long)mt * nt * s, rest = blocks % round;
-      const double loop = c.k32[i] * elems * tps * ks / 32;
+      const int64_t blocks = tiles * s, rest = blocks & (two ? 511 : 255);
+      const double loop = k32 * tps;
       const double all = c.block[i] + loop, alone = c.block[i] + (two ? c.alone : 1.0) * loop;
-      const double est =
-          (double)(blocks / round) * all + (rest == 0 ? 0.0 : rest <= 256 ? alone : all) +
-          (s > 1 ? c.split + c.each * s + traffic * (2 * s + 1) : 0.0);
+      const double est = parts + (double)(blocks >> (two ? 9 : 8)) * all +
+                         (rest == 0 ? 0.0 : rest <= 256 ? alone : all);
       if (best_t == 0 || est < best_t) {
         best_t = est;
         best = GemmPlan{bm, ko, mt, nt, s, tps * ks, 0};
@@ -719,12 +724,12 @@ static void gemm_launch(const GemmPlan& p, const GemmArgs& g, hipStream_t st) {
 // C (ldc) = epi(A * B): the GEMM applies the epilogue itself when the
 // reduction is not split; otherwise it writes per-split partial sums to the
 // workspace and gemm_splitk_epilogue adds them in order and applies it.
-// colsum (may be null): column sums of B, likewise.
+// colsum (may be null): column sums of B, likewise.  p: the product's plan.
 template <bool AK, bool BK, class E, class CE>
-static sb_status gemm_run(GemmArgs g, float* ws, size_t ws_bytes, hipStream_t st) {
+static sb_status gemm_run(GemmArgs g, const GemmPlan& p, float* ws, size_t ws_bytes,
+                          hipStream_t st) {
   // Masks exist only where gemm_launch instantiates them.
   if ((g.amask && !(AK && BK)) || (g.bmask && (AK || BK))) return SB_ERR_UNSUPPORTED;
-  const GemmPlan p = product_plan(g.M, g.N, g.K, g.lda, AK, g.ldb, BK, (int)sizeof(E));
   if (p.ws_bytes > 0 && (!ws || ws_bytes < p.ws_bytes)) return SB_ERR_WORKSPACE;
   // Buffer ranges cover whole operands.
   const int64_t a_elems = AK ? (int64_t)(g.M - 1) * g.lda + g.K : (int64_t)(g.K - 1) * g.lda + g.M;
@@ -773,28 +778,39 @@ static sb_status fc_check(const sb_fc_desc* d) {
   return SB_OK;
 }
 
+// The plans of the three products: Y, dX partial, dW.
+static GemmPlan plan_y(const sb_fc_desc* d) {
+  return product_plan(d->m, d->n_shard, d->k_in, d->ldx, true, d->n_shard, false,
+                      (int)sbh::dsize(d->dtype));
+}
+static GemmPlan plan_dx(const sb_fc_desc* d) {
+  return product_plan(d->m, d->k_in, d->n_shard, d->ldy, true, d->n_shard, true,
+                      (int)sbh::dsize(d->dtype));
+}
+static GemmPlan plan_dw(const sb_fc_desc* d) {
+  return product_plan(d->k_in, d->n_shard, d->m, d->ldx, false, d->ldy, false,
+                      (int)sbh::dsize(d->dtype));
+}
+
 extern "C" size_t sb_fc_workspace_bytes(const sb_fc_desc* d, int pass) {
   if (fc_check(d) != SB_OK) return (size_t)-1;
-  const int es = d->dtype == SB_BF16 ? 2 : 4;
-  const int m = d->m, kin = d->k_in, ns = d->n_shard;
-  if (pass == SB_FC_FWD) return product_plan(m, ns, kin, d->ldx, true, ns, false, es).ws_bytes;
+  if (pass == SB_FC_FWD) return plan_y(d).ws_bytes;
   if (pass == SB_FC_BWD)   // dX partial, then dW: the two share the workspace
-    return std::max(product_plan(m, kin, ns, d->ldy, true, ns, true, es).ws_bytes,
-                    product_plan(kin, ns, m, d->ldx, false, d->ldy, false, es).ws_bytes);
+    return std::max(plan_dx(d).ws_bytes, plan_dw(d).ws_bytes);
   return (size_t)-1;
 }
 
 // Forward on operands of type E (fp32, or bf16 bits with a bf16 output).
 template <class E>
-static sb_status fc_fwd_run(const sb_fc_desc* d, const void* x, const void* w, const float* b,
-                            void* y, void* ws, size_t ws_bytes, hipStream_t st) {
+static sb_status fc_fwd_run(const sb_fc_desc* d, const GemmPlan& p, const void* x, const void* w, const float* b, void* y, void* ws, size_t ws_bytes,
+                            hipStream_t st) {
   GemmArgs g{};
   g.a = x; g.lda = d->ldx; g.amask = nullptr;
   g.b = w; g.ldb = d->n_shard; g.bmask = nullptr;
   g.c = y; g.ldc = d->ldy;
   g.M = d->m; g.N = d->n_shard; g.K = d->k_in;
   g.bias = b; g.relu = (d->flags & SB_FUSE_RELU) ? 1 : 0; g.accumulate = 0;
-  return gemm_run<true, false, E, E>(g, (float*)ws, ws_bytes, st);
+  return gemm_run<true, false, E, E>(g, p, (float*)ws, ws_bytes, st);
 }
 
 extern "C" sb_status sb_fc_shard_fwd(const sb_fc_desc* d, const void* x, const void* w,
@@ -811,14 +827,15 @@ extern "C" sb_status sb_fc_shard_fwd(const sb_fc_desc* d, const void* x, const v
       sbh::overlaps(y, yb, b, b ? d->n_shard * sizeof(float) : 0))
     return SB_ERR_INVALID_ARG;
   // The workspace (split partials) must not overlap any operand.
-  const size_t need = sb_fc_workspace_bytes(d, SB_FC_FWD);
+  const GemmPlan p = plan_y(d);
+  const size_t need = p.ws_bytes;
   if (need > 0 && (sbh::overlaps(ws, need, x, xb) || sbh::overlaps(ws, need, w, wb) ||
                    sbh::overlaps(ws, need, y, yb) ||
                    sbh::overlaps(ws, need, b, b ? d->n_shard * sizeof(float) : 0)))
     return SB_ERR_INVALID_ARG;
   hipStream_t st = sbh::stream_of(stream);
-  s = d->dtype == SB_BF16 ? fc_fwd_run<u16>(d, x, w, b, y, ws, ws_bytes, st)
-                          : fc_fwd_run<float>(d, x, w, b, y, ws, ws_bytes, st);
+  s = d->dtype == SB_BF16 ? fc_fwd_run<u16>(d, p, x, w, b, y, ws, ws_bytes, st)
+                          : fc_fwd_run<float>(d, p, x, w, b, y, ws, ws_bytes, st);
   if (s != SB_OK) return s;
   return sbh::launch_status();
 }
@@ -826,7 +843,7 @@ extern "C" sb_status sb_fc_shard_fwd(const sb_fc_desc* d, const void* x, const v
 // Backward on operands of type E: dx_partial has type E, dW and db fp32.
 // db is added up inside the dW product.
 template <class E>
-static sb_status fc_bwd_run(const sb_fc_desc* d, const void* x, const void* w, const void* dy,
+static sb_status fc_bwd_run(const sb_fc_desc* d, const GemmPlan& px, const GemmPlan& pw, const void* x, const void* w, const void* dy,
                             const void* mask, void* dxp, float* dw, float* db, int accumulate,
                             void* ws, size_t ws_bytes, hipStream_t st) {
   sb_status s;
@@ -836,7 +853,7 @@ static sb_status fc_bwd_run(const sb_fc_desc* d, const void* x, const void* w, c
     g.b = w; g.ldb = d->n_shard; g.bmask = nullptr;
     g.c = dxp; g.ldc = d->ldx;
     g.M = d->m; g.N = d->k_in; g.K = d->n_shard;
-    s = gemm_run<true, true, E, E>(g, (float*)ws, ws_bytes, st);
+    s = gemm_run<true, true, E, E>(g, px, (float*)ws, ws_bytes, st);
     if (s != SB_OK) return s;
   }
   GemmArgs g{};
@@ -846,7 +863,7 @@ static sb_status fc_bwd_run(const sb_fc_desc* d, const void* x, const void* w, c
   g.M = d->k_in; g.N = d->n_shard; g.K = d->m;
   g.accumulate = accumulate;
   g.colsum = db; g.colsum_acc = accumulate;
-  return gemm_run<false, false, E, float>(g, (float*)ws, ws_bytes, st);
+  return gemm_run<false, false, E, float>(g, pw, (float*)ws, ws_bytes, st);
 }
 
 extern "C" sb_status sb_fc_shard_bwd(const sb_fc_desc* d, const void* x, const void* w,
@@ -874,7 +891,8 @@ extern "C" sb_status sb_fc_shard_bwd(const sb_fc_desc* d, const void* x, const v
     for (int o2 = o + 1; o2 < 3; ++o2)
       if (sbh::overlaps(outs[o], outsb[o], outs[o2], outsb[o2])) return SB_ERR_INVALID_ARG;
   }
-  size_t need = sb_fc_workspace_bytes(d, SB_FC_BWD);
+  const GemmPlan px = plan_dx(d), pw = plan_dw(d);
+  const size_t need = std::max(px.ws_bytes, pw.ws_bytes);
   if (need > 0 && (!ws || ws_bytes < need)) return SB_ERR_WORKSPACE;
   // The workspace (split partials) must not overlap any operand.
   if (need > 0) {
@@ -885,8 +903,8 @@ extern "C" sb_status sb_fc_shard_bwd(const sb_fc_desc* d, const void* x, const v
   }
   hipStream_t st = sbh::stream_of(stream);
   s = d->dtype == SB_BF16
-          ? fc_bwd_run<u16>(d, x, w, dy, mask, dxp, dw, db, accumulate, ws, ws_bytes, st)
-          : fc_bwd_run<float>(d, x, w, dy, mask, dxp, dw, db, accumulate, ws, ws_bytes, st);
+          ? fc_bwd_run<u16>(d, px, pw, x, w, dy, mask, dxp, dw, db, accumulate, ws, ws_bytes, st)
+          : fc_bwd_run<float>(d, px, pw, x, w, dy, mask, dxp, dw, db, accumulate, ws, ws_bytes, st);
   if (s != SB_OK) return s;
   return sbh::launch_status();
 }
