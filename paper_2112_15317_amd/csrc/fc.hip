@@ -600,10 +600,11 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
 //     one has it to itself; split partials a launch, `each`, and their traffic,
 //     `odd` times as much where outputs are added one by one.
 // Fitted to 15000 timings of the three products of 104 shards under forced plans
-// in both types; 1.7 and 1.2 us more for a launch, since a caller that does not
-// capture its calls is bound by them (K = 2 modulo iterations of 128 rows: 78
-// launches and 545 us, 70 and 517 without the splits that save less).  The plan
-// taken is 1.3 % slower than the best one on average, 19 % at most, where one block a CU at the same cost for all operands lost 4 % (fp32)
+// in both types; fp32 splits have to save 1.7 us more, since a caller that does
+// not capture its calls is bound by launches (K = 2 modulo iterations of 128
+// rows: 78 launches and 545 us, 70 and 517 without the splits that save less; a
+// bf16 shard of 200 x 1500 x 700 rather needs them, 31 us and 35).  The plan taken
+// is 0.8 (bf16) or 1.4 % slower than the best one on average, 19 % at most, where one block a CU at the same cost for all operands lost 4 % (fp32)
 // and 12 % (bf16), up to 2.1 times.
 struct GemmPlan { int bm, ko, mt, nt, splits, kps; size_t ws_bytes; };
 struct GemmCost { double block[2], k32[2], elems[2][3], alone, split, each, tb_s, odd; };
@@ -611,7 +612,7 @@ static const GemmCost kGCost[2] = {
     {{3.44, 1.35}, {1.74, 1.08}, {{0.63, 1.28, 1.61}, {0.88, 1.17, 1.61}},       // fp32
      0.68, 3.86, 0.11, 5.61, 1.58},
     {{3.69, 1.30}, {0.95, 0.63}, {{1.28, 1.47, 2.17}, {1.37, 1.65, 2.91}},       // bf16
-     0.72, 3.70, 0.13, 5.24, 3.5}};
+     0.72, 2.50, 0.13, 5.24, 3.5}};
 
 // ak, bk: A, B contiguous along k; aligned: their rows allow vector staging.
 static GemmPlan gemm_plan(int M, int N, int K, int esize, bool ak, bool bk, bool aligned) {
