@@ -69,11 +69,10 @@ class ConvStack:
     stream, forked after its output gradient is ready and joined at the end,
     so it overlaps the data-gradient chain (the two only share inputs, and
     each has its own split-reduction workspace).  Off by default: the large
-    kernels are planned as one full round of blocks over the CUs (two per
-    CU), so a kernel running beside one pushes some of its blocks into a
-    second round; on the fp32 CIFAR step the overlapped backward is about 5 %
-    slower than one stream, on the bf16 ImageNet-shaped step about 1 %
-    faster.
+    kernels are planned as one full round of blocks over the CUs, so a kernel
+    running beside one pushes some of its blocks into a second round; the
+    fp32 CIFAR step takes 1.525 ms overlapped and 1.495 on one stream, the
+    bf16 ImageNet-shaped step 3.91 and 3.86.
     """
 
     def __init__(self, schedule, n, in_ch, hw, dtype="f32", device="cuda",
