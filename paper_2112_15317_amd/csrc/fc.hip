@@ -604,8 +604,9 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue(
 // not capture its calls is bound by launches (K = 2 modulo iterations of 128
 // rows: 78 launches and 545 us, 70 and 517 without the splits that save less; a
 // bf16 shard of 200 x 1500 x 700 rather needs them, 31 us and 35).  The plan taken
-// is 0.8 (bf16) or 1.4 % slower than the best one on average, 19 % at most, where one block a CU at the same cost for all operands lost 4 % (fp32)
-// and 12 % (bf16), up to 2.1 times.
+// is 0.8 (bf16) or 1.4 % slower than the best one on average, 19 % at most, where
+// one block a CU at the same cost for all operands lost 4 % (fp32) and 12 %
+// (bf16), up to 2.1 times.
 struct GemmPlan { int bm, ko, mt, nt, splits, kps; size_t ws_bytes; };
 struct GemmCost { double block[2], k32[2], elems[2][3], alone, split, each, tb_s, odd; };
 static const GemmCost kGCost[2] = {
@@ -803,8 +804,8 @@ extern "C" size_t sb_fc_workspace_bytes(const sb_fc_desc* d, int pass) {
 
 // Forward on operands of type E (fp32, or bf16 bits with a bf16 output).
 template <class E>
-static sb_status fc_fwd_run(const sb_fc_desc* d, const GemmPlan& p, const void* x, const void* w, const float* b, void* y, void* ws, size_t ws_bytes,
-                            hipStream_t st) {
+static sb_status fc_fwd_run(const sb_fc_desc* d, const GemmPlan& p, const void* x, const void* w,
+                            const float* b, void* y, void* ws, size_t ws_bytes, hipStream_t st) {
   GemmArgs g{};
   g.a = x; g.lda = d->ldx; g.amask = nullptr;
   g.b = w; g.ldb = d->n_shard; g.bmask = nullptr;
@@ -844,9 +845,10 @@ extern "C" sb_status sb_fc_shard_fwd(const sb_fc_desc* d, const void* x, const v
 // Backward on operands of type E: dx_partial has type E, dW and db fp32.
 // db is added up inside the dW product.
 template <class E>
-static sb_status fc_bwd_run(const sb_fc_desc* d, const GemmPlan& px, const GemmPlan& pw, const void* x, const void* w, const void* dy,
-                            const void* mask, void* dxp, float* dw, float* db, int accumulate,
-                            void* ws, size_t ws_bytes, hipStream_t st) {
+static sb_status fc_bwd_run(const sb_fc_desc* d, const GemmPlan& px, const GemmPlan& pw,
+                            const void* x, const void* w, const void* dy, const void* mask,
+                            void* dxp, float* dw, float* db, int accumulate, void* ws,
+                            size_t ws_bytes, hipStream_t st) {
   sb_status s;
   if (dxp) {
     GemmArgs g{};
